@@ -9,14 +9,12 @@
 //
 // A drafting step has few rows (R = B r <= 128 per pass), so every
 // projection streams its weight once and is bound by HBM.  One kernel
-// serves all five: work-groups of eight waves, 4..8 of which own 16 output
-// columns each, and a range of 256-channel chunks of the reduction; lane
-// (c, G) of a wave reads 128 contiguous bytes of weight row c per chunk
-// (every row in 512-byte runs) straight into registers, the chunk of all
-// input rows is copied into LDS by the global_load_lds DMA, and
-// z^T = W x^T runs on bf16 matrix cores.  A compute unit streams weights at
-// a bounded rate, so the planner sizes the column groups and reduction
-// splits to give every unit the same load; each split writes fp32 partial
+// serves all five, around the weight stream of skinny_stream.hpp: a
+// work-group of eight waves, of which up to seven own 32 output columns each
+// over a range of 256-channel chunks of the reduction and one copies the
+// input rows.  A compute unit streams weights at a bounded rate, so the
+// planner sizes the column groups and reduction splits to give every unit
+// the same load; each split writes fp32 partial
 // sums, and one or two epilogue launches per projection add the splits
 // and apply what follows it: bias + RMSNorm, RoPE + cache append, residual
 // + RMSNorm, SwiGLU, or the final residual.  The attention is the
@@ -28,158 +26,89 @@
 
 #include "device_common.hpp"
 #include "launch.hpp"
+#include "skinny_stream.hpp"
 
 namespace sd {
 namespace {
 
-typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(1))) const void gbl_cvoid;
-
-constexpr int kChunkK = 256;    // reduction channels per step
+// Projection work-groups own up to 224 output columns: seven waves of 32
+// (two 16-column blocks), or, for int8 rows against at most 64 input rows,
+// fourteen waves of 16, and one more wave that copies the input.  Int8 rows
+// spend vector instructions on the conversion, which twice the waves
+// overlap better; with more input rows the registers do not allow them.
+// Columns per work-group, splits and order of the sums are the same for
+// both, so bf16 and int8 weights of the same values give the same bits.
+constexpr int kLinearCols = 32;        // the plan's column unit
+constexpr int kLinearMaxUnits = 7;
+template <int RB, bool Q8>
+struct LinearCfg {
+  static constexpr int CB = Q8 && RB <= 4 ? 1 : 2;             // 16-column blocks per wave
+  static constexpr int NW = kLinearMaxUnits * (2 / CB) + (CB == 1 ? 2 : 1);   // 8 or 16 waves
+};
 constexpr int kEpiThreads = 256;
 
 // part[ks][r][n] = sum over split ks's chunks of x[r][k] w[n][k], for the
-// rows r0 .. r0 + 16 RB - 1 of this pass.  Matrix-core product i of a chunk
-// takes the i-th 16-byte load of every lane (channels 64 G + 8 i .. +7 of
-// the chunk), a fixed permutation of the chunk's channels that the input
-// fragments follow; the input chunk's 16-byte pieces of row t sit at slot
-// piece ^ (t & 15), so the fragment reads are free of bank conflicts.
-// Two int8 values (bytes k, k + 1 of v) as two bf16 values, exactly (every
-// int8 value has at most 8 significant bits): sign-extend, convert to
-// float32, keep the upper halves.
-__device__ __forceinline__ uint32_t i8x2_to_bf16x2(uint32_t v, int k) {
-  const float f0 = (float)(int)(int8_t)(v >> (8 * k));
-  const float f1 = (float)(int)(int8_t)(v >> (8 * k + 8));
-  return __builtin_amdgcn_perm(__float_as_uint(f1), __float_as_uint(f0), 0x07060302u);
-}
-
-// Q8: the weight holds int8 rows with one fp32 scale per row (output
-// column); each lane then loads 64 bytes of its row per chunk (4 loads),
-// widens them to bf16 in registers and scales the accumulators once.
-// A work-group owns a.cols = 16 x (active waves) output columns; waves past
-// them only copy their share of the input chunks and meet the barriers, so
-// the planner can size the groups to fill every compute unit evenly.
-template <int RB, int NW, bool Q8>
-__global__ __launch_bounds__(NW * 64) void linear_partial(LinearArgs a) {
-  constexpr int HROWS = RB * 16;
-  constexpr int HPIECES = HROWS * 32;          // 16-byte pieces of one input chunk
-  constexpr int DMA = HPIECES / (NW * 64);     // copies per thread and chunk
-  static_assert(HPIECES % (NW * 64) == 0, "whole copies per thread");
-  __shared__ __align__(16) unsigned char hbuf[2][HPIECES * 16];
+// rows r0 .. r0 + 16 RB - 1 of this pass.  Q8: the weight holds int8 rows
+// with one fp32 scale per row (output column), applied to the accumulators.
+// A work-group owns a.cols output columns; waves past them only meet the
+// barriers, so the planner can size the groups to fill every compute unit
+// evenly.
+template <int RB, bool Q8>
+__global__ __launch_bounds__((LinearCfg<RB, Q8>::NW * 64)) void linear_partial(LinearArgs a) {
+  constexpr int NW = LinearCfg<RB, Q8>::NW, CB = LinearCfg<RB, Q8>::CB;
+  __shared__ __align__(16) unsigned char ring[stream_ring_bytes(RB)];
   const int tid = threadIdx.x;
   const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), G = lane >> 4, c = lane & 15;
-  const int n0 = blockIdx.x * a.cols + w * 16;
-  const bool active = w * 16 < a.cols;         // wave-uniform
+  const int n0 = blockIdx.x * a.cols + w * 16 * CB;
   const int ks = blockIdx.y;
-  const int r0 = blockIdx.z * HROWS;
+  const int r0 = blockIdx.z * RB * 16;
   const int K = a.K, N = a.N, R = a.R;
-  const int nch = K / kChunkK;
-  const int ch0 = (int)((long long)nch * ks / a.ksplit);
-  const int ch1 = (int)((long long)nch * (ks + 1) / a.ksplit);
-  const uint16_t* W = static_cast<const uint16_t*>(a.w);
-  const uint16_t* X = static_cast<const uint16_t*>(a.x);
-  // weight row n0 + c (clamped; columns >= N are not written)
-  const u32x4* wsrc = Q8 ? reinterpret_cast<const u32x4*>(static_cast<const int8_t*>(a.w) +
-                                                          (size_t)min(n0 + c, N - 1) * K + 64 * G)
-                         : reinterpret_cast<const u32x4*>(W + (size_t)min(n0 + c, N - 1) * K + 64 * G);
-  constexpr int WL = Q8 ? 4 : 8;               // 16-byte weight loads per lane and chunk
-  // copy j of this thread moves piece P = (w DMA + j) 64 + lane of a chunk:
-  // input row P / 32 of the pass (clamped; padded rows are not written)
-  const uint16_t* hsrc[DMA];
+  const int nch = K / kStreamChunk;
+  const int ch0 = (int)((unsigned)nch * (unsigned)ks / (unsigned)a.ksplit);   // nch <= 2^12, ksplit <= 16
+  const int ch1 = (int)((unsigned)nch * (unsigned)(ks + 1) / (unsigned)a.ksplit);
+  // Work-groups in step would read the same channels of every row, rows a
+  // power of two apart, which keeps few HBM channels busy: with up to four
+  // splits each starts at a chunk of its own (6 rows: 57344 x 8192, one
+  // split, 179.6 -> 164.3 us; 10240 x 8192, four, 35.1 -> 31.5 us).  More
+  // splits spread the starts by themselves, and their work-groups share the
+  // input chunks in L2 better in step (112 rows, 4096 x 14336, eight
+  // splits: 33.0 us in step, 35.0 us rotated).
+  const int rot = a.ksplit <= 4 && ch0 < ch1 ? (int)(blockIdx.x % (unsigned)(ch1 - ch0)) : 0;
+  const bool active = w < NW - 1 && w * 16 * CB < a.cols;   // wave-uniform
+  floatx4 acc[CB][RB];
 #pragma unroll
-  for (int j = 0; j < DMA; ++j) {
-    const int P = (w * DMA + j) * 64 + lane;
-    const int row = P >> 5, slot = P & 31;
-    hsrc[j] = X + (size_t)min(r0 + row, R - 1) * K + ((slot ^ (row & 15)) * 8);
-  }
-  auto issue = [&](int n, int buf) {
+  for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-    for (int j = 0; j < DMA; ++j)
-      __builtin_amdgcn_global_load_lds((gbl_cvoid*)(hsrc[j] + (size_t)n * kChunkK),
-                                       (lds_void*)(&hbuf[buf][(w * DMA + j) * 1024]), 16, 0, 0);
-  };
-
-  floatx4 acc[RB];
+    for (int rb = 0; rb < RB; ++rb) acc[cb][rb] = floatx4{0.f, 0.f, 0.f, 0.f};
+  if (ch0 < ch1)
+    stream_product<RB, CB, NW, Q8>(static_cast<const unsigned char*>(a.w) + (size_t)n0 * K * (Q8 ? 1 : 2), N - n0,
+                                     active, static_cast<const uint16_t*>(a.x) + (size_t)r0 * K, min(R - r0, RB * 16),
+                                     K, ch0, ch1, rot, ring, acc);
+  if (!active) return;
+  // accumulator element i of lane (c, G): input row rb*16 + c, column n0 +
+  // 16 cb + 4G + i
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) acc[rb] = floatx4{0.f, 0.f, 0.f, 0.f};
-  // the weights of chunk n + 1 are loaded before chunk n is multiplied, so
-  // two chunks of every lane's row are in flight
-  auto wload = [&](u32x4 (&wf)[WL], int n) {
+  for (int cb = 0; cb < CB; ++cb) {
+    const int n = n0 + 16 * cb + 4 * G;
+    if constexpr (Q8) {
+      floatx4 sc;
 #pragma unroll
-    for (int i = 0; i < WL; ++i) wf[i] = wsrc[(size_t)n * (4 * WL) + i];
-  };
-  auto step = [&](const u32x4 (&wf)[WL], u32x4 (&wnext)[WL], int n) {
-    const int buf = (n - ch0) & 1;
-    if (n + 1 < ch1) {
-      wload(wnext, n + 1);
-      // the next weights are the WL newest loads: this thread's copies of
-      // chunk n (and its weights) have landed; after the barrier every
-      // wave's have, and every wave is done reading the other buffer
-      wait_vm_then_barrier<WL>();
-    } else {
-      wait_vm_then_barrier<0>();
+      for (int i = 0; i < 4; ++i) sc[i] = a.wscale[min(n + i, N - 1)];
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) acc[cb][rb] *= sc;
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      Pack8 x;
-      if constexpr (Q8) {
-        // product i takes bytes 8 (i & 1) .. + 7 of load i / 2: channels
-        // 64 G + 8 i .. + 7 as in the bf16 layout
-        const u32x4& v = wf[i >> 1];
-        const uint32_t lo = v[(i & 1) * 2], hi = v[(i & 1) * 2 + 1];
-        x.u = u32x4{i8x2_to_bf16x2(lo, 0), i8x2_to_bf16x2(lo, 2), i8x2_to_bf16x2(hi, 0), i8x2_to_bf16x2(hi, 2)};
+    for (int rb = 0; rb < RB; ++rb) {
+      const int r = r0 + rb * 16 + c;
+      if (r >= R || n >= N) continue;
+      float* dst = a.part + ((size_t)ks * R + r) * N + n;
+      if (n + 3 < N && (reinterpret_cast<uintptr_t>(dst) & 15) == 0) {
+        *reinterpret_cast<floatx4*>(dst) = acc[cb][rb];
       } else {
-        x.u = wf[i];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (n + i < N) dst[i] = acc[cb][rb][i];
       }
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        const int row = rb * 16 + c;
-        Pack8 y;
-        y.u = *reinterpret_cast<const u32x4*>(&hbuf[buf][(row * 32 + ((8 * G + i) ^ c)) * 16]);
-        acc[rb] = mfma_bf16(x.b, y.b, acc[rb]);
-      }
-    }
-    if (n + 1 < ch1) issue(n + 1, buf ^ 1);
-  };
-  if (!active) {
-    // input copies and barriers only, in the same order as the other waves
-    if (ch0 < ch1) issue(ch0, 0);
-#pragma unroll 1
-    for (int n = ch0; n < ch1; ++n) {
-      wait_vm_then_barrier<0>();
-      if (n + 1 < ch1) issue(n + 1, ((n - ch0) & 1) ^ 1);
-    }
-    return;
-  }
-  u32x4 wa[WL], wb[WL];
-  if (ch0 < ch1) {
-    wload(wa, ch0);
-    issue(ch0, 0);
-  }
-#pragma unroll 1
-  for (int n = ch0; n < ch1; n += 2) {
-    step(wa, wb, n);
-    if (n + 1 < ch1) step(wb, wa, n + 1);
-  }
-  // accumulator element i of lane (c, G): input row rb*16 + c, column n0 + 4G + i
-  if constexpr (Q8) {
-    floatx4 sc;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) sc[i] = a.wscale[min(n0 + 4 * G + i, N - 1)];
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) acc[rb] *= sc;
-  }
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    const int r = r0 + rb * 16 + c;
-    if (r >= R || n0 + 4 * G >= N) continue;
-    float* dst = a.part + ((size_t)ks * R + r) * N + n0 + 4 * G;
-    if (n0 + 4 * G + 3 < N && (reinterpret_cast<uintptr_t>(dst) & 15) == 0) {
-      *reinterpret_cast<floatx4*>(dst) = acc[rb];
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (n0 + 4 * G + i < N) dst[i] = acc[rb][i];
     }
   }
 }
@@ -386,43 +315,25 @@ __global__ __launch_bounds__(kEpiThreads) void kp_post(const float* probs, const
   if (j == 0 && threadIdx.x == 0) pos_out[b] = pos_in[b] + advance;
 }
 
-template <int NW, bool Q8>
-hipError_t launch_partial_nw(const LinearArgs& a, int rb, int passes, hipStream_t st) {
-  const dim3 grid((a.N + a.cols - 1) / a.cols, a.ksplit, passes);
-  const dim3 block(NW * 64);
-  switch (rb) {
-    case 1: hipLaunchKernelGGL((linear_partial<1, NW, Q8>), grid, block, 0, st, a); break;
-    case 2: hipLaunchKernelGGL((linear_partial<2, NW, Q8>), grid, block, 0, st, a); break;
-    case 3: hipLaunchKernelGGL((linear_partial<3, NW, Q8>), grid, block, 0, st, a); break;
-    case 4: hipLaunchKernelGGL((linear_partial<4, NW, Q8>), grid, block, 0, st, a); break;
-    case 5: hipLaunchKernelGGL((linear_partial<5, NW, Q8>), grid, block, 0, st, a); break;
-    case 6: hipLaunchKernelGGL((linear_partial<6, NW, Q8>), grid, block, 0, st, a); break;
-    case 7: hipLaunchKernelGGL((linear_partial<7, NW, Q8>), grid, block, 0, st, a); break;
-    default: hipLaunchKernelGGL((linear_partial<8, NW, Q8>), grid, block, 0, st, a); break;
-  }
+template <int RB, bool Q8>
+hipError_t launch_partial_rb(const LinearArgs& a, int passes, hipStream_t st) {
+  hipLaunchKernelGGL((linear_partial<RB, Q8>), dim3((a.N + a.cols - 1) / a.cols, a.ksplit, passes),
+                     dim3(LinearCfg<RB, Q8>::NW * 64), 0, st, a);
   return hipGetLastError();
 }
 
-// Work-groups of the bf16 projection kernel resident per compute unit, as
-// the runtime computes them from its registers, LDS and waves (for eight-
-// wave groups the registers bind: two per unit, where the LDS of two input
-// chunks would hold three); 0 when the runtime cannot tell.
-template <int NW>
-int resident_per_cu(int rb) {
-  const void* f = nullptr;
+template <bool Q8>
+hipError_t launch_partial(const LinearArgs& a, int rb, int passes, hipStream_t st) {
   switch (rb) {
-    case 1: f = reinterpret_cast<const void*>(&linear_partial<1, NW, false>); break;
-    case 2: f = reinterpret_cast<const void*>(&linear_partial<2, NW, false>); break;
-    case 3: f = reinterpret_cast<const void*>(&linear_partial<3, NW, false>); break;
-    case 4: f = reinterpret_cast<const void*>(&linear_partial<4, NW, false>); break;
-    case 5: f = reinterpret_cast<const void*>(&linear_partial<5, NW, false>); break;
-    case 6: f = reinterpret_cast<const void*>(&linear_partial<6, NW, false>); break;
-    case 7: f = reinterpret_cast<const void*>(&linear_partial<7, NW, false>); break;
-    default: f = reinterpret_cast<const void*>(&linear_partial<8, NW, false>); break;
+    case 1: return launch_partial_rb<1, Q8>(a, passes, st);
+    case 2: return launch_partial_rb<2, Q8>(a, passes, st);
+    case 3: return launch_partial_rb<3, Q8>(a, passes, st);
+    case 4: return launch_partial_rb<4, Q8>(a, passes, st);
+    case 5: return launch_partial_rb<5, Q8>(a, passes, st);
+    case 6: return launch_partial_rb<6, Q8>(a, passes, st);
+    case 7: return launch_partial_rb<7, Q8>(a, passes, st);
+    default: return launch_partial_rb<8, Q8>(a, passes, st);
   }
-  int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, NW * 64, 0) != hipSuccess) return 0;
-  return n;
 }
 
 }  // namespace
@@ -432,40 +343,31 @@ LinearPlan plan_linear(int R, int K, int N, int cus) {
   const int rows = std::min(R, kLinearRowsPerPass);
   p.row_blocks = (rows + 15) / 16;
   p.passes = (R + kLinearRowsPerPass - 1) / kLinearRowsPerPass;
-  // work-groups resident per compute unit: the runtime's figure, else the
-  // LDS bound (two input chunks of row_blocks * 8 KB) and 32 waves
-  const int lds_fit = (160 * 1024) / (p.row_blocks * 16 * 1024);
-  auto resident = [&](int waves) {
-    int per_cu = resident_per_cu<8>(p.row_blocks);
-    if (per_cu <= 0) per_cu = std::max(1, std::min(lds_fit, 32 / waves));
-    return (long long)std::max(cus, 1) * per_cu;
-  };
-  // eight waves per work-group, each chunk of the inputs copied once for
-  // all of them
-  p.waves = 8;
-  const long long cap = resident(p.waves);
-  const int nch = K / kChunkK;
+  constexpr int wide = kLinearCols;
+  // one work-group per compute unit: its registers hold no second one
+  const long long cap = std::max(cus, 1);
+  const int nch = K / kStreamChunk;
   const long long ncu = std::max(cus, 1);
   // A compute unit streams its weight rows at a bounded rate, so the time
-  // follows the most loaded unit: (work-groups it runs) x (rows x chunks
-  // per work-group).  For 4..8 column-owning waves, split the reduction to
-  // fill the resident slots in one round (at least four chunks per split)
-  // and keep the count with the least such load; ties go to more waves
-  // (more weight loads in flight per unit).  One wave fewer than eight
-  // fills every unit evenly where 128-column groups would leave units with
-  // one group less than others (57344 columns: 512 groups of 112 instead
-  // of 448 of 128).
+  // follows the most loaded unit: (work-groups it runs) x (chunks per
+  // work-group) x (bytes per chunk: its weight rows, and the input rows,
+  // which come from L2 and cost about half as much each).  For 2..7 column
+  // units, split the reduction to fill the device in one round (at least
+  // four chunks per split) and keep the count with the least such load; ties
+  // go to more units (more weight loads in flight).  One unit fewer than
+  // possible fills every compute unit evenly where wider groups would leave
+  // some with one group less than others.
   long long best = -1;
-  for (int nwa = 8; nwa >= 4; --nwa) {
-    const long long g = (long long)((N + nwa * 16 - 1) / (nwa * 16)) * p.passes;
+  for (int nwa = kLinearMaxUnits; nwa >= 2; --nwa) {
+    const long long g = (long long)((N + nwa * wide - 1) / (nwa * wide)) * p.passes;
     long long ks = std::max(1LL, cap / g);
     ks = std::min<long long>(ks, std::max(1, nch / 4));
     ks = std::max(1LL, std::min<long long>(ks, kLinearMaxSplits));
     const long long per_cu = (g * ks + ncu - 1) / ncu;
-    const long long load = (long long)nwa * ((nch + ks - 1) / ks) * per_cu;
+    const long long load = per_cu * ((nch + ks - 1) / ks) * (2 * nwa * wide + p.row_blocks * 16);
     if (best < 0 || load < best) {
       best = load;
-      p.cols = nwa * 16;
+      p.cols = nwa * wide;
       p.ksplit = (int)ks;
     }
   }
@@ -476,8 +378,8 @@ LinearPlan plan_linear(int R, int K, int N, int cus) {
 hipError_t launch_linear_partial(const LinearArgs& args, const LinearPlan& p, hipStream_t st) {
   LinearArgs a = args;
   a.cols = p.cols;
-  if (a.wscale != nullptr) return launch_partial_nw<8, true>(a, p.row_blocks, p.passes, st);
-  return launch_partial_nw<8, false>(a, p.row_blocks, p.passes, st);
+  if (a.wscale != nullptr) return launch_partial<true>(a, p.row_blocks, p.passes, st);
+  return launch_partial<false>(a, p.row_blocks, p.passes, st);
 }
 
 hipError_t launch_epi_add(const float* part, int ksplit, int R, int N, const float* bias, const float* residual,

@@ -148,7 +148,6 @@ struct LinearArgs {
 struct LinearPlan {
   int row_blocks;  // 16-row blocks per pass (1..8)
   int passes;      // passes over the weight (ceil(R / 128))
-  int waves;       // waves per work-group
   int cols;        // output columns per work-group: 16 per wave that owns columns
   int ksplit;      // splits of the reduction
   size_t part_bytes;
