@@ -67,13 +67,13 @@ __global__ __launch_bounds__((LinearCfg<RB, Q8>::NW * 64)) void linear_partial(L
   const int ch0 = (int)((unsigned)nch * (unsigned)ks / (unsigned)a.ksplit);   // nch <= 2^12, ksplit <= 16
   const int ch1 = (int)((unsigned)nch * (unsigned)(ks + 1) / (unsigned)a.ksplit);
   // Work-groups in step would read the same channels of every row, rows a
-  // power of two apart, which keeps few HBM channels busy: with up to four
-  // splits each starts at a chunk of its own (6 rows: 57344 x 8192, one
-  // split, 179.6 -> 164.3 us; 10240 x 8192, four, 35.1 -> 31.5 us).  More
-  // splits spread the starts by themselves, and their work-groups share the
-  // input chunks in L2 better in step (112 rows, 4096 x 14336, eight
-  // splits: 33.0 us in step, 35.0 us rotated).
-  const int rot = a.ksplit <= 4 && ch0 < ch1 ? (int)(blockIdx.x % (unsigned)(ch1 - ch0)) : 0;
+  // multiple of a kilobyte apart, which keeps few channels of their XCD's L2
+  // busy.  With up to four splits, consecutive work-groups of one XCD (every
+  // eighth) start at consecutive chunks (6 rows: 57344 x 8192, one split,
+  // 179.6 -> 162 us; 8192 x 8192, four, 31.5 -> 25.4 us).  More splits spread
+  // the starts by themselves, and share the input chunks in L2 better in
+  // step (112 rows, 4096 x 14336, eight splits: 33.0 us, rotated 34.8 us).
+  const int rot = a.ksplit <= 4 && ch0 < ch1 ? (int)((blockIdx.x >> 3) % (unsigned)(ch1 - ch0)) : 0;
   const bool active = w < NW - 1 && w * 16 * CB < a.cols;   // wave-uniform
   floatx4 acc[CB][RB];
 #pragma unroll

@@ -90,7 +90,6 @@ struct LmHeadArgs {
   float scale_log2;    // log2(e) / temperature
   float* stats;        // workspace: [R][pairs] (max, sum) pairs, pairs <= ceil(V/16) (per block or per work-group)
   int cus;             // compute units of the device (0: no per-unit balancing)
-  int nfull;           // set by the launch: work-groups with a block for every wave (< 0: all)
 };
 
 size_t lm_head_workspace_bytes(int R, int V);

@@ -12,10 +12,9 @@
 //    are written to `probs` as fp32, with (max, sum of 2^(s - max)) pairs
 //    of every row: one per work-group (its waves' blocks merged in LDS) or
 //    one per 16-entry vocabulary block.
-//    - `lm_logits_burst` (R <= 64, d % 256 == 0): 16 vocabulary rows per
-//      wave read in 512-byte runs per row, straight into registers; the
-//      hidden chunk of 256 channels of all rows staged through LDS by DMA;
-//      one pair per row and work-group.
+//    - `lm_logits_stream` (R <= 128, d % 256 == 0): the weight stream of the
+//      projections, 32 vocabulary rows per wave; one pair per row and
+//      work-group.
 //    - `lm_logits_bf16` (the other shapes): 16 or 32 vocabulary rows per
 //      wave read 128 bytes per row at a time, the next 64 channels in
 //      flight while the current ones are multiplied; the hidden chunk of 64
@@ -31,6 +30,7 @@
 
 #include "device_common.hpp"
 #include "launch.hpp"
+#include "skinny_stream.hpp"
 
 namespace sd {
 namespace {
@@ -194,13 +194,9 @@ __global__ __launch_bounds__(256) void lm_logits_bf16(LmHeadArgs a) {
   }
 }
 
-typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(1))) const void gbl_cvoid;
-
 // Scaled logits of 16 vocabulary rows (accumulator rows) x 16 hidden rows
 // (columns) to probs, with the (max, sum) of the 16-entry vocabulary block
 // for every hidden row
-template <bool STATS>
 __device__ __forceinline__ Stat write_block(const LmHeadArgs& a, const floatx4& acc, int vbase, int r) {
   const int lane = threadIdx.x & 63, G = lane >> 4;
   const int V = a.V;
@@ -220,136 +216,62 @@ __device__ __forceinline__ Stat write_block(const LmHeadArgs& a, const floatx4& 
       for (int i = 0; i < 4; ++i)
         if (vbase + 4 * G + i < V) dst[i] = s[i];
     }
-    if (STATS && G == 0) reinterpret_cast<float2*>(a.stats)[(size_t)r * ((V + 15) / 16) + vbase / 16] = make_float2(st.m, st.l);
   }
   return st;
 }
 
-// Logits for R <= 64 hidden rows and widths d % 256 == 0, shaped for long
-// contiguous weight reads.  Each wave owns VB blocks of 16 vocabulary rows;
-// per chunk of 256 channels lane (c, G) loads 128 contiguous bytes of row c
-// of each block (channels 64 G .. 64 G + 63) as eight back-to-back 16-byte
-// loads, so every row is read in 512-byte runs (about 20% more HBM
-// bandwidth than 128-byte runs on this weight layout).  Matrix-core product i takes the i-th load of every
-// lane, i.e. channels {64 G + 8 i .. 64 G + 8 i + 7}: a fixed permutation of
-// the chunk's channels, which the hidden fragments follow.  The hidden chunk
-// of all rows (RB x 16 rows x 512 bytes) goes HBM/L2 -> LDS by the
-// global_load_lds DMA into two buffers; pieces of row r sit at slot
-// piece ^ (r & 15) so the 16 rows read at one piece hit 16 distinct bank
-// groups.
-//
-// With a.nfull >= 0 the first a.nfull work-groups give every wave its VB
-// blocks and the later ones leave their last wave without blocks (it only
-// moves its share of the hidden chunks): the grid then holds a whole number
-// of work-groups per compute unit with the larger ones dispatched first, so
-// no unit streams more than one 16-row block above the mean.
-template <int RB, int NW, int VB>
-__global__ __launch_bounds__(NW * 64) void lm_logits_burst(LmHeadArgs a) {
-  constexpr int HROWS = RB * 16;
-  constexpr int HPIECES = HROWS * 32;          // 16-byte pieces of one hidden chunk
-  constexpr int DMA = HPIECES / (NW * 64);     // copies per thread and chunk
-  static_assert(HPIECES % (NW * 64) == 0, "whole copies per thread");
-  __shared__ __align__(16) unsigned char hbuf[2][HPIECES * 16];
-  __shared__ Stat wst[NW][HROWS];              // per wave: its blocks' statistics of every hidden row
+// Logits for R <= 128 hidden rows and widths d % 256 == 0, on the weight
+// stream of the projections (skinny_stream.hpp): each wave owns 32
+// vocabulary rows (a unit), the last wave copies the hidden rows.  The
+// first `extra` work-groups hold base + 1 units, the others base: the grid
+// is a whole number of work-groups per compute unit with the larger ones
+// dispatched first, so no compute unit streams more than one unit above the
+// mean.  Consecutive work-groups of one XCD start at consecutive chunks of
+// the reduction (see linear_partial: in step they read the same channels of
+// rows a multiple of a kilobyte apart, few channels of their L2; 16 rows,
+// V = 60000, d = 4096: 114 us in step, 153 us with the starts spread over the
+// XCDs only, 96 us so).
+// Per call, before (16 vocabulary rows per wave, hidden chunks copied by every
+// wave; 128-byte runs for R > 64) and after: d = 4096: 112 rows, V = 32000
+// 105.0 -> 74.4 us; 28 rows, V = 60000 112.8 -> 100.4 us; 12 rows, V = 100001
+// 190.4 -> 156.2 us.  d = 8192, V = 152064: 112 rows 713 -> 551 us, 36 rows
+// 466 -> 461 us, 5 rows 430 -> 445 us (slower).
+template <int RB>
+__global__ __launch_bounds__(512) void lm_logits_stream(LmHeadArgs a, int base, int extra) {
+  constexpr int NW = 8, CB = 2, HROWS = RB * 16;
+  __shared__ __align__(16) unsigned char ring[stream_ring_bytes(RB)];
+  __shared__ Stat wst[NW - 1][HROWS];
   const int tid = threadIdx.x;
   const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), G = lane >> 4, c = lane & 15;
   const int wg = blockIdx.x;
-  const bool full = a.nfull < 0 || wg < a.nfull;
-  const int unit0 = full ? wg * NW : a.nfull * NW + (wg - a.nfull) * (NW - 1);
-  const int v0 = (unit0 + w) * (VB * 16);
-  const int d = a.d, V = a.V, R = a.R;
-  const uint16_t* W = static_cast<const uint16_t*>(a.weight);
-  const uint16_t* H = static_cast<const uint16_t*>(a.hidden);
-  // row c of each block of this wave (clamped; results of rows >= V are
-  // discarded)
-  const u32x4* wsrc[VB];
+  const int units = base + (wg < extra ? 1 : 0);
+  const int v0 = (wg * base + min(wg, extra) + w) * (16 * CB);
+  const bool active = w < units;               // wave-uniform; units <= NW - 1
+  const int nch = a.d / kStreamChunk;
+  floatx4 acc[CB][RB];
 #pragma unroll
-  for (int vb = 0; vb < VB; ++vb)
-    wsrc[vb] = reinterpret_cast<const u32x4*>(W + (size_t)min(v0 + vb * 16 + c, V - 1) * d + 64 * G);
-  // copy j of this thread moves piece P = (w * DMA + j) * 64 + lane of the
-  // chunk: hidden row P / 32 (clamped; padded rows are discarded), LDS slot
-  // P % 32 holding global piece slot ^ (row & 15)
-  const uint16_t* hsrc[DMA];
+  for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-  for (int j = 0; j < DMA; ++j) {
-    const int P = (w * DMA + j) * 64 + lane;
-    const int row = P >> 5, slot = P & 31;
-    hsrc[j] = H + (size_t)min(row, R - 1) * d + ((slot ^ (row & 15)) * 8);
-  }
-  auto issue_hidden = [&](int n, int buf) {
-#pragma unroll
-    for (int j = 0; j < DMA; ++j)
-      __builtin_amdgcn_global_load_lds((gbl_cvoid*)(hsrc[j] + n * 256),
-                                       (lds_void*)(&hbuf[buf][(w * DMA + j) * 1024]), 16, 0, 0);
-  };
-
-  floatx4 acc[VB][RB];
-#pragma unroll
-  for (int vb = 0; vb < VB; ++vb)
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) acc[vb][rb] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const int nch = d / 256;
-  issue_hidden(0, 0);
-  const bool idle = !full && w == NW - 1;
-  if (idle) {
-    // same copies, waits and barriers as the other waves, no weight rows
-#pragma unroll 1
-    for (int n = 0; n < nch; ++n) {
-      wait_vm_then_barrier<0>();
-      if (n + 1 < nch) issue_hidden(n + 1, (n & 1) ^ 1);
-    }
-  } else {
-#pragma unroll 1
-  for (int n = 0; n < nch; ++n) {
-    const int buf = n & 1;
-    u32x4 wf[VB][8];
-#pragma unroll
-    for (int vb = 0; vb < VB; ++vb)
-#pragma unroll
-      for (int i = 0; i < 8; ++i) wf[vb][i] = wsrc[vb][n * 32 + i];
-    // the weight loads are the newest: everything older (this thread's
-    // copies of chunk n) has landed; after the barrier every wave's copies
-    // have, and every wave is done reading the other buffer
-    wait_vm_then_barrier<8 * VB>();
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        const int row = rb * 16 + c;
-        Pack8 y;
-        y.u = *reinterpret_cast<const u32x4*>(&hbuf[buf][(row * 32 + ((8 * G + i) ^ c)) * 16]);
-#pragma unroll
-        for (int vb = 0; vb < VB; ++vb) {
-          Pack8 x;
-          x.u = wf[vb][i];
-          acc[vb][rb] = mfma_bf16(x.b, y.b, acc[vb][rb]);
-        }
-      }
-    }
-    if (n + 1 < nch) issue_hidden(n + 1, buf ^ 1);
-  }
-  }
+    for (int rb = 0; rb < RB; ++rb) acc[cb][rb] = floatx4{0.f, 0.f, 0.f, 0.f};
+  stream_product<RB, CB, NW, false>(static_cast<const uint16_t*>(a.weight) + (size_t)v0 * a.d, a.V - v0, active,
+                                    static_cast<const uint16_t*>(a.hidden), a.R, a.d, 0, nch,
+                                    (int)((unsigned)(wg >> 3) % (unsigned)nch), ring, acc);
   // scaled logits to probs; the statistics of this work-group's blocks,
   // merged over its waves, as one (max, sum) pair per hidden row at
   // stats[r * gridDim.x + blockIdx.x]
-  Stat st[RB];
+  if (active) {
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) st[rb] = Stat{-INFINITY, 0.f};
-  if (!idle) {
+    for (int rb = 0; rb < RB; ++rb) {
+      Stat st{-INFINITY, 0.f};
 #pragma unroll
-    for (int vb = 0; vb < VB; ++vb)
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) st[rb] = merge(st[rb], write_block<false>(a, acc[vb][rb], v0 + vb * 16, rb * 16 + c));
-  }
-  if (G == 0) {
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) wst[w][rb * 16 + c] = st[rb];
+      for (int cb = 0; cb < CB; ++cb) st = merge(st, write_block(a, acc[cb][rb], v0 + cb * 16, rb * 16 + c));
+      if (G == 0) wst[w][rb * 16 + c] = st;
+    }
   }
   __syncthreads();
-  if (tid < HROWS && tid < R) {
+  if (tid < HROWS && tid < a.R) {
     Stat t = wst[0][tid];
-#pragma unroll
-    for (int i = 1; i < NW; ++i) t = merge(t, wst[i][tid]);
+    for (int i = 1; i < units; ++i) t = merge(t, wst[i][tid]);
     reinterpret_cast<float2*>(a.stats)[(size_t)tid * gridDim.x + blockIdx.x] = make_float2(t.m, t.l);
   }
 }
@@ -446,32 +368,20 @@ __global__ __launch_bounds__(256) void lm_normalize(LmHeadArgs a, int npairs) {
 // 16-entry block otherwise).
 template <int RB>
 hipError_t launch_rb(const LmHeadArgs& a, hipStream_t st, int* npairs) {
-  *npairs = (a.V + 15) / 16;
-  if constexpr (RB <= 4) {
-    if (a.d % 256 == 0) {
-      LmHeadArgs b = a;
-      b.nfull = -1;
-      if (a.V >= 65536) {
-        // G work-groups, a multiple of the unit count, of 8 or 7 blocks
-        // (nfull = nb - 7 G of 8) when such a G covers the nb blocks
-        const int nb = (a.V + 15) / 16, g8 = (nb + 7) / 8;
-        int grid = g8;
-        if (a.cus > 0) {
-          const int G = (g8 + a.cus - 1) / a.cus * a.cus;
-          if (G > g8 && 7LL * G <= nb) {
-            grid = G;
-            b.nfull = nb - 7 * G;
-          }
-        }
-        hipLaunchKernelGGL((lm_logits_burst<RB, 8, 1>), dim3(grid), dim3(512), 0, st, b);
-        *npairs = grid;
-      } else {
-        hipLaunchKernelGGL((lm_logits_burst<RB, 4, 1>), dim3((a.V + 63) / 64), dim3(256), 0, st, b);
-        *npairs = (a.V + 63) / 64;
-      }
+  if constexpr (RB <= 8) {
+    if (a.d % kStreamChunk == 0) {
+      // rounds of up to seven units per work-group, one work-group per
+      // compute unit (its registers hold no second one; two smaller ones, of
+      // one 16-row block per wave, measured the same to 6% slower)
+      const int cus = a.cus > 0 ? a.cus : 256;
+      const int units = (a.V + 31) / 32, per_cu = (units + cus - 1) / cus;
+      const int groups = std::min(units, (per_cu + 6) / 7 * cus);
+      *npairs = groups;
+      hipLaunchKernelGGL((lm_logits_stream<RB>), dim3(groups), dim3(512), 0, st, a, units / groups, units % groups);
       return hipGetLastError();
     }
   }
+  *npairs = (a.V + 15) / 16;
   if ((a.V + 127) / 128 >= 1024) {
     hipLaunchKernelGGL((lm_logits_bf16<RB, 2>), dim3((a.V + 127) / 128), dim3(256), 0, st, a);
   } else {

@@ -63,7 +63,13 @@ __device__ __forceinline__ void stream_for(F&& f) {
 // Weights go to registers in groups of eight 16-byte loads per lane and
 // 16-row block, 512 bytes of each row (two steps of bf16, four of int8).
 // Two groups of registers take turns: one is loaded while the other is
-// multiplied.  The lanes' share of a group is such that both types sum the
+// multiplied, its loads back to back at the group's start, one 16-row block
+// after the other, so that a row's 512 bytes reach HBM together (issued piece
+// by piece over both blocks, bf16 is up to 24% slower: 6 rows, 8192 x 28672
+// 82 -> 102 us).  Int8 rows of 16 or of more
+// than 64 input rows are refilled piece by piece: their products take so
+// long that the burst would come late (6 rows, 8192 x 28672 53 -> 47 us; 112
+// rows, 57344 x 8192 142 -> 128 us).  The lanes' share of a group is such that both types sum the
 // same products in the same order, and that a load touches one 128-byte
 // line per row.
 //
@@ -101,6 +107,7 @@ __device__ __forceinline__ void stream_product(const void* w0, int valid, bool a
   constexpr int WS = 8 / GS;                    // weight loads per step, lane and 16-row block
   constexpr int SLOT = stream_slot_bytes(RB);
   constexpr uint32_t PAST = 0x80000000u;        // beyond every buffer's range
+  constexpr bool ROLL = Q8 && (RB == 1 || (RB >= 5 && RB <= 7));   // refill piece by piece
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), G = lane >> 4,
             c = lane & 15;
   const int t0 = ch0 * 2, t1 = ch1 * 2;         // steps of the range
@@ -164,16 +171,18 @@ __device__ __forceinline__ void stream_product(const void* w0, int valid, bool a
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb) woff[cb] = (uint32_t)(cb * 16 + c) * row_bytes + (uint32_t)G * (Q8 ? 16u : 32u);
   u32x4 wf[2][CB][8];
-  auto wload = [&](u32x4 (&f)[CB][8], int t) {  // the group of steps t .. t + GS - 1
+  // piece i of block cb of the group of steps t .. t + GS - 1
+  auto wpiece = [&](u32x4 (&f)[CB][8], int t, int cb, int i) {
+    const int ts = t + i / WS;
+    const uint32_t off = ts < t1 ? (uint32_t)at(ts) * (Q8 ? 128u : 256u) : PAST;
+    const uint32_t in_step = Q8 ? 64u * (i & 1) : 128u * ((i & 3) >> 1) + 16u * (i & 1);
+    f[cb][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, (int)(woff[cb] + off + in_step), 0, 0));
+  };
+  auto wload = [&](u32x4 (&f)[CB][8], int t) {  // a whole group, block by block
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int ts = t + i / WS;
-        const uint32_t off = ts < t1 ? (uint32_t)at(ts) * (Q8 ? 128u : 256u) : PAST;
-        const uint32_t in_step = Q8 ? 64u * (i & 1) : 128u * ((i & 3) >> 1) + 16u * (i & 1);
-        f[cb][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, (int)(woff[cb] + off + in_step), 0, 0));
-      }
+      for (int i = 0; i < 8; ++i) wpiece(f, t, cb, i);
   };
   uint32_t xa[4];                               // fragment addresses of the four products, slot 0
 #pragma unroll
@@ -181,7 +190,7 @@ __device__ __forceinline__ void stream_product(const void* w0, int valid, bool a
 
   // products of one step: s its index within the weight group.  The step's
   // 4 RB fragments are read four at a time, one such unit ahead.
-  auto multiply = [&](const u32x4 (&f)[CB][8], auto stag, auto slot_tag) {
+  auto multiply = [&](u32x4 (&f)[CB][8], int tg, auto stag, auto slot_tag) {
     constexpr int s = decltype(stag)::value, SO = decltype(slot_tag)::value * SLOT;
     u32x4 xf[2][4];
     Pack8 p[CB];
@@ -227,18 +236,33 @@ __device__ __forceinline__ void stream_product(const void* w0, int valid, bool a
           y.u = xf[u & 1][i];
           acc[cb][rb] = mfma_bf16(p[cb].b, y.b, acc[cb][rb]);
         }
+        // a piece's registers are free after its last product
+        if constexpr (ROLL && rb == RB - 1 && j % 2 == 1) {
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb) wpiece(f, tg + 2 * GS, cb, s * WS + (j >> 1));
+        }
       });
       __builtin_amdgcn_sched_barrier(0);
     });
   };
-  wload(wf[0], t0);
+  if constexpr (ROLL) {
+    // in the order of the products, which the waits of the loop count on
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) wpiece(wf[i / 8], t0 + i / 8 * GS, cb, i % 8);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  } else {
+    wload(wf[0], t0);
+  }
 #pragma unroll 1
   for (int t = t0; t < t1; t += 2 * GS)
     stream_for<0, 2 * GS>([&](auto st) {
       constexpr int s = decltype(st)::value, gs = s % GS;
       meet();
-      if constexpr (gs == 0) wload(wf[(s / GS + 1) & 1], t + s + GS);
-      multiply(wf[s / GS], std::integral_constant<int, gs>{}, std::integral_constant<int, s & 3>{});
+      if constexpr (!ROLL && gs == 0) wload(wf[(s / GS + 1) & 1], t + s + GS);
+      multiply(wf[s / GS], t + s - gs, std::integral_constant<int, gs>{}, std::integral_constant<int, s & 3>{});
     });
 }
 
