@@ -15,10 +15,11 @@
 // input rows.  A compute unit streams weights at a bounded rate, so the
 // planner sizes the column groups and reduction splits to give every unit
 // the same load; each split writes fp32 partial
-// sums, and one or two epilogue launches per projection add the splits
-// and apply what follows it: bias + RMSNorm, RoPE + cache append, residual
-// + RMSNorm, SwiGLU, or the final residual.  The attention is the
-// verification kernel (its merge writing the bf16 input of Wo): the new
+// sums, and one epilogue launch per projection adds the splits and applies
+// what follows it: bias + norm weight, RoPE + cache append, residual + norm
+// weight, SwiGLU, or the final residual (an RMSNorm's row factor commutes
+// with the projection after it, so that projection's epilogue applies it).  The attention is the
+// verification kernel (writing the bf16 input of Wo itself): the new
 // rows are a block of r queries, causal inside the block, over the cache.
 #include <math.h>
 
@@ -135,12 +136,17 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
 // grid (ceil(N / kEpiCols), R), kEpiThreads threads of four columns each.
 // Every split of a thread's columns is loaded before any is added (the
 // splits are added in split order), so a row's partials stream from many
-// compute units at once.  With `ss`, block x of row r also writes the sum
-// of squares of its columns to ss[r * gridDim.x + x] for epi_norm_cols.
+// compute units at once.  With `h`, it also prepares the next projection's
+// input under an RMSNorm: h = bf16(y * norm_w), and block x of row r writes
+// the sum of squares of its columns to ss[r * gridDim.x + x].  The factor
+// 1 / sqrt(mean(y^2) + eps), one per row, commutes with the projection, whose
+// epilogue applies it (row_scale); a launch of its own for it took 3.8 us (6
+// rows) to 4.8 us (112 rows) in the layer, twice.
 constexpr int kEpiCols = 4 * kEpiThreads;
 __global__ __launch_bounds__(kEpiThreads) void epi_add_cols(const float* part, int ksplit, int R, int N,
                                                             const float* bias, const float* residual,
-                                                            float* out, float* ss) {
+                                                            float* out, const float* norm_w, __bf16* h,
+                                                            float* ss) {
   __shared__ float red[kEpiThreads / 64];
   const int r = blockIdx.y;
   const size_t stride = (size_t)R * N;
@@ -162,6 +168,12 @@ __global__ __launch_bounds__(kEpiThreads) void epi_add_cols(const float* part, i
       if (bias) y += *reinterpret_cast<const floatx4*>(bias + n0);
       if (residual) y += *reinterpret_cast<const floatx4*>(residual + row + n0);
       *reinterpret_cast<floatx4*>(out + row + n0) = y;
+      if (h != nullptr) {
+        Pack8 pk;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) pk.b[j] = float_to_bf16(y[j] * norm_w[n0 + j]);
+        *reinterpret_cast<u32x2*>(h + row + n0) = u32x2{pk.u[0], pk.u[1]};
+      }
       s2 = y[0] * y[0] + y[1] * y[1] + y[2] * y[2] + y[3] * y[3];
     }
   } else {
@@ -173,31 +185,25 @@ __global__ __launch_bounds__(kEpiThreads) void epi_add_cols(const float* part, i
       if (bias) y += bias[n];
       if (residual) y += residual[row + n];
       out[row + n] = y;
+      if (h != nullptr) h[row + n] = float_to_bf16(y * norm_w[n]);
       s2 += y * y;
     }
   }
-  if (ss == nullptr) return;
+  if (h == nullptr) return;
   const float t = block_sum(s2, red);
   if (threadIdx.x == 0) ss[(size_t)r * gridDim.x + blockIdx.x] = t;
 }
 
-// h = y / sqrt(mean(y^2) + eps) * norm_w in bf16, for the rows epi_add_cols
-// wrote with their block sums of squares (nblk per row, added in block
-// order); same grid as epi_add_cols.
-__global__ __launch_bounds__(kEpiThreads) void epi_norm_cols(const float* y, int N, const float* ss, int nblk,
-                                                             const float* norm_w, float eps, __bf16* h) {
-  const int r = blockIdx.y;
+// 1 / sqrt(mean(y^2) + eps) of row r of width d from epi_add_cols' nblk block
+// sums (added in block order).
+__device__ __forceinline__ float row_scale(const float* ss, int nblk, int r, int d, float eps) {
   float t = 0.f;
   for (int i = 0; i < nblk; ++i) t += ss[(size_t)r * nblk + i];
-  const float inv = 1.f / sqrtf(t / (float)N + eps);
-  const int n0 = blockIdx.x * kEpiCols + threadIdx.x * 4;
-  const size_t row = (size_t)r * N;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int n = n0 + j;
-    if (n < N) h[row + n] = float_to_bf16(y[row + n] * inv * norm_w[n]);
-  }
+  return 1.f / sqrtf(t / (float)d + eps);
 }
+// A row whose mean square overflows has scale 0: its normalised values are 0
+// even where the unscaled projection overflowed.
+__device__ __forceinline__ float scaled(float x, float inv) { return inv == 0.f ? 0.f : x * inv; }
 
 static int epi_blocks(int N) { return (N + kEpiCols - 1) / kEpiCols; }
 
@@ -213,13 +219,15 @@ static int epi_blocks(int N) { return (N + kEpiCols - 1) / kEpiCols; }
 __global__ __launch_bounds__(kEpiThreads) void epi_rope_qkv(const float* part, int ksplit, int R, int N,
                                                             const int32_t* pos, int rows, int Hq, int Hkv,
                                                             int D, double log_theta, int Lmax, __bf16* q,
-                                                            __bf16* kc, __bf16* vc, int32_t* kv_len) {
+                                                            __bf16* kc, __bf16* vc, int32_t* kv_len,
+                                                            const float* ss, int nblk, int d, float eps) {
   __shared__ float2 rot[64];                   // (cos, sin) of each pair's angle
   const int r = blockIdx.y;
   const int b = r / rows, j = r - b * rows;
   const int p = pos[b] + j;
   const bool store = p >= 0 && p < Lmax;
   if (j == 0 && blockIdx.x == 0 && threadIdx.x == 0) kv_len[b] = pos[b] + rows;
+  const float inv = row_scale(ss, nblk, r, d, eps);
   const size_t stride = (size_t)R * N;
   const int half = D / 2;
   if (threadIdx.x < half) {
@@ -239,8 +247,8 @@ __global__ __launch_bounds__(kEpiThreads) void epi_rope_qkv(const float* part, i
   if (t < pairs) {
     const int hh = t / half, i = t - hh * half;
     const size_t base = (size_t)r * N + (size_t)hh * D;
-    const float x0 = split_sum(part, ksplit, stride, base + i);
-    const float x1 = split_sum(part, ksplit, stride, base + i + half);
+    const float x0 = scaled(split_sum(part, ksplit, stride, base + i), inv);
+    const float x1 = scaled(split_sum(part, ksplit, stride, base + i + half), inv);
     const float cs = rot[i].x, sn = rot[i].y;
     const float y0 = x0 * cs - x1 * sn, y1 = x1 * cs + x0 * sn;
     if (hh < Hq) {
@@ -254,21 +262,23 @@ __global__ __launch_bounds__(kEpiThreads) void epi_rope_qkv(const float* part, i
     }
   } else if (store && t < pairs + Hkv * D) {
     const int hv = (t - pairs) / D, e = (t - pairs) - hv * D;
-    const float v = split_sum(part, ksplit, stride, (size_t)r * N + (size_t)(Hq + Hkv + hv) * D + e);
+    const float v = scaled(split_sum(part, ksplit, stride, (size_t)r * N + (size_t)(Hq + Hkv + hv) * D + e), inv);
     vc[(((size_t)b * Lmax + p) * Hkv + hv) * D + e] = float_to_bf16(v);
   }
 }
 
 // act[r][i] = silu(g) * u with g, u the split sums of columns i and I + i
+// times the row's norm factor
 __global__ __launch_bounds__(kEpiThreads) void epi_swiglu(const float* part, int ksplit, int R, int I,
-                                                          __bf16* act) {
+                                                          __bf16* act, const float* ss, int nblk, int d, float eps) {
   const int r = blockIdx.y;
   const int i = blockIdx.x * kEpiThreads + threadIdx.x;
   if (i >= I) return;
   const size_t N = 2 * (size_t)I;
   const size_t stride = (size_t)R * N;
-  const float g = split_sum(part, ksplit, stride, (size_t)r * N + i);
-  const float u = split_sum(part, ksplit, stride, (size_t)r * N + I + i);
+  const float inv = row_scale(ss, nblk, r, d, eps);
+  const float g = scaled(split_sum(part, ksplit, stride, (size_t)r * N + i), inv);
+  const float u = scaled(split_sum(part, ksplit, stride, (size_t)r * N + I + i), inv);
   act[(size_t)r * I + i] = float_to_bf16(g / (1.f + expf(-g)) * u);
 }
 
@@ -385,7 +395,7 @@ hipError_t launch_linear_partial(const LinearArgs& args, const LinearPlan& p, hi
 hipError_t launch_epi_add(const float* part, int ksplit, int R, int N, const float* bias, const float* residual,
                           float* out, hipStream_t st) {
   hipLaunchKernelGGL(epi_add_cols, dim3(epi_blocks(N), R), dim3(kEpiThreads), 0, st, part, ksplit, R, N, bias,
-                     residual, out, (float*)nullptr);
+                     residual, out, (const float*)nullptr, (__bf16*)nullptr, (float*)nullptr);
   return hipGetLastError();
 }
 
@@ -440,17 +450,16 @@ hipError_t launch_semi_ar(const SemiArArgs& a, const SemiArPlan& p, hipStream_t 
     LinearArgs la{x, w, part, R, K, N, lp.ksplit, scale};
     return launch_linear_partial(la, lp, st);
   };
-  // x0 = FC(u), h = RMSNorm(x0)
+  // x0 = FC(u), h = x0 ln1 (the norm's row factors follow the projection)
   if ((e = lin(a.u, a.fc_w, a.fc_s, 2 * d, d, p.fc)) != hipSuccess) return e;
   hipLaunchKernelGGL(epi_add_cols, eg, dim3(kEpiThreads), 0, st, part, p.fc.ksplit, R, d, a.fc_b,
-                     (const float*)nullptr, x0, ss);
-  hipLaunchKernelGGL(epi_norm_cols, eg, dim3(kEpiThreads), 0, st, x0, d, ss, (int)eg.x, a.ln1, a.eps, h);
+                     (const float*)nullptr, x0, a.ln1, h, ss);
   // q, k, v with RoPE; k, v appended to the cache
   if ((e = lin(h, a.wqkv, a.wqkv_s, d, nqkv, p.qkv)) != hipSuccess) return e;
   const int rope_threads = (a.Hq + a.Hkv) * (D / 2) + a.Hkv * D;
   hipLaunchKernelGGL(epi_rope_qkv, dim3((rope_threads + kEpiThreads - 1) / kEpiThreads, R), dim3(kEpiThreads), 0, st, part, p.qkv.ksplit, R, nqkv, a.pos, a.r,
                      a.Hq, a.Hkv, D, log((double)a.theta), a.Lmax, q,
-                     static_cast<__bf16*>(a.k_cache), static_cast<__bf16*>(a.v_cache), kv_len);
+                     static_cast<__bf16*>(a.k_cache), static_cast<__bf16*>(a.v_cache), kv_len, ss, (int)eg.x, d, a.eps);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // attention of the r new rows over the cache, causal inside them
   VerifyArgs va{};
@@ -473,15 +482,14 @@ hipError_t launch_semi_ar(const SemiArArgs& a, const SemiArPlan& p, hipStream_t 
   va.part_o = reinterpret_cast<float*>(ws + p.off_verify);
   va.part_lse = va.part_o + p.verify.part_rows * D;
   if ((e = launch_verify(va, p.verify, 1, st)) != hipSuccess) return e;
-  // x1 = x0 + attn Wo^T, h = RMSNorm(x1)
+  // x1 = x0 + attn Wo^T, h = x1 ln2
   if ((e = lin(attn16, a.wo, a.wo_s, a.Hq * D, d, p.o)) != hipSuccess) return e;
   hipLaunchKernelGGL(epi_add_cols, eg, dim3(kEpiThreads), 0, st, part, p.o.ksplit, R, d,
-                     (const float*)nullptr, x0, x1, ss);
-  hipLaunchKernelGGL(epi_norm_cols, eg, dim3(kEpiThreads), 0, st, x1, d, ss, (int)eg.x, a.ln2, a.eps, h);
+                     (const float*)nullptr, x0, x1, a.ln2, h, ss);
   // act = SwiGLU(h), out = x1 + act Wdown^T
   if ((e = lin(h, a.wgu, a.wgu_s, d, 2 * a.I, p.gu)) != hipSuccess) return e;
   hipLaunchKernelGGL(epi_swiglu, dim3((a.I + kEpiThreads - 1) / kEpiThreads, R), dim3(kEpiThreads), 0, st, part,
-                     p.gu.ksplit, R, a.I, act);
+                     p.gu.ksplit, R, a.I, act, ss, (int)eg.x, d, a.eps);
   if ((e = lin(act, a.wdown, a.wdown_s, a.I, d, p.down)) != hipSuccess) return e;
   return launch_epi_add(part, p.down.ksplit, R, d, nullptr, x1, a.out, st);
 }
