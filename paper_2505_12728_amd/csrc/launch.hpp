@@ -20,6 +20,7 @@ struct VerifyPlan {
   int rows_wg;          // bf16 path: rows per work-group (row_blocks * 16)
   int key_groups;       // bf16 path: wave groups taking alternate tiles
   int stream_wgs;       // bf16 path: grid size (work-groups on the device)
+  bool direct;          // bf16 path, short caches: one work-group per pair, no merge
   size_t part_rows;     // rows of partial results in the workspace
   size_t workspace_bytes;
   bool ok;              // false: the shape exceeds the kernels' index range

@@ -28,6 +28,8 @@
 // Kernel 2 (merge): finds the partials of each pair from the same tile
 //   arithmetic, combines them with the log-sum-exp rule and writes out / lse
 //   in the caller's [B, k, Hq] layout.
+// Short caches (up to 256 positions) take kernel 1 alone, one work-group per
+//   pair with four key groups that are combined in LDS.
 //
 // fp32 caches take a plain (non matrix-core) split kernel with the same
 // partial format; it computes in float64 so fp32 inputs keep fp32 accuracy.
@@ -228,7 +230,11 @@ __device__ __forceinline__ void advance(const VerifyArgs& a, int X, int cap, Til
 // running maximum is raised (and O, l rescaled) only when a row's scores
 // exceed it by more than 2^8 (the stale maximum is exact for the final
 // o = O / l; p stays below 256).
-template <int D, int NWR, int KG, int NBUF, bool PAGED>
+//
+// DIRECT (short caches): the grid holds one work-group per pair, which takes
+// all of the pair's tiles, combines its key groups in LDS and writes the
+// final rows, so there is no merge launch.
+template <int D, int NWR, int KG, int NBUF, bool PAGED, bool DIRECT>
 __global__ __launch_bounds__(NWR * KG * 64) void verify_stream_bf16(VerifyArgs a, int G,
                                                                     int row_groups) {
   constexpr int NW = NWR * KG;
@@ -266,7 +272,14 @@ __global__ __launch_bounds__(NWR * KG * 64) void verify_stream_bf16(VerifyArgs a
   const int hw = blockIdx.x;
   const int wg = (gridDim.x & 63) == 0 ? ((hw & ~63) | ((hw & 7) << 3) | ((hw >> 3) & 7)) : hw;
   TileStart ts;
-  if (!tile_start_small(a, X, cap, wg, G, kgrp, &ts)) {
+  if constexpr (DIRECT) {
+    const int b = hw / X;
+    const int L = seq_len_s(a, b, cap), nt = (L + 31) >> 5;
+    ts.n0 = 0;
+    ts.n1 = nt;
+    ts.ca = TileCursor{b, hw - b * X, 0, nt, L};
+    ts.cb = TileCursor{b, hw - b * X, min(kgrp, nt - 1), nt, L};
+  } else if (!tile_start_small(a, X, cap, wg, G, kgrp, &ts)) {
     ts.T = tiles_before(a, X, cap, a.B);
     ts.n0 = (int)((long long)ts.T * wg / G);
     ts.n1 = (int)((long long)ts.T * (wg + 1) / G);
@@ -277,7 +290,7 @@ __global__ __launch_bounds__(NWR * KG * 64) void verify_stream_bf16(VerifyArgs a
   }
   const int n0 = __builtin_amdgcn_readfirstlane(ts.n0);
   const int n1 = __builtin_amdgcn_readfirstlane(ts.n1);
-  if (n0 >= n1) return;
+  if (!DIRECT && n0 >= n1) return;
   const int last = n1 - 1;
 
   // per-lane constants of the copies: copy i of this wave (ii = w *
@@ -411,6 +424,26 @@ __global__ __launch_bounds__(NWR * KG * 64) void verify_stream_bf16(VerifyArgs a
     if (G4 == 0) a.part_lse[prow] = lsum > 0.f ? m + log2f(lsum) : -INFINITY;
   };
 
+  // final rows of the pair (DIRECT): O / l with l summed over the row
+  auto write_rows = [&](float lsum) {
+    if (!row_ok) return;
+    const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+      const floatx4 v = o[db] * inv;
+      const size_t at = (size_t)orow * D + db * 16 + 4 * G4;
+      if (a.out_bf16 != nullptr) {
+        Pack8 pk;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) pk.b[e] = float_to_bf16(v[e]);
+        *reinterpret_cast<u32x2*>(a.out_bf16 + at) = u32x2{pk.u[0], pk.u[1]};
+      } else {
+        *reinterpret_cast<floatx4*>(a.out + at) = v;
+      }
+    }
+    if (a.lse != nullptr && G4 == 0) a.lse[orow] = lsum > 0.f ? (m + log2f(lsum)) * kLn2 : -INFINITY;
+  };
+
   auto compute = [&](int t0, const unsigned char* slot) {
     const uint32_t sb = lds_addr(slot);
     u32x4 kr[2][DC];
@@ -525,6 +558,15 @@ __global__ __launch_bounds__(NWR * KG * 64) void verify_stream_bf16(VerifyArgs a
   // adds no waits of its own between them and the copies.  A new segment
   // (query loads, partial stores) drains this wave's memory counter first,
   // so the counted waits only ever see copies.
+  if constexpr (DIRECT) {
+    if (n0 >= n1) {                            // empty sequence: no visible key in any row
+      if (kgrp == 0) {
+        start_segment(ts.ca);
+        write_rows(0.f);
+      }
+      return;
+    }
+  }
   TileCursor ic = uniform(ts.ca);              // issue cursor at tile in
   int in = n0;
   TileCursor cc = uniform(ts.cb);              // compute cursor at tile cn
@@ -569,7 +611,46 @@ __global__ __launch_bounds__(NWR * KG * 64) void verify_stream_bf16(VerifyArgs a
   }
   // no copy may still be writing this work-group's LDS when it exits
   __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));   // vmcnt(0)
-  if constexpr (KG == 2) {
+  if constexpr (DIRECT) {
+    // key groups 1 .. KG - 1 hand their (max, sum, O) to group 0 through the
+    // ring; a group without tiles hands over a zero sum
+    __syncthreads();                           // every wave is done with the ring
+    floatx4* xo = reinterpret_cast<floatx4*>(&ring[0][0]);
+    float2* xml = reinterpret_cast<float2*>(&ring[0][0] + (KG - 1) * NWR * DB * 1024);
+    static_assert((KG - 1) * NWR * (DB * 1024 + 512) <= NBUF * BUF_BYTES, "hand-over fits the ring");
+    const float lsum = cur_pair >= 0 ? wave_sum_across_groups(l) : 0.f;
+    if (kgrp > 0) {
+      const int slot = (kgrp - 1) * NWR + wr;
+      if (cur_pair >= 0) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db) xo[(slot * DB + db) * 64 + lane] = o[db];
+      }
+      xml[slot * 64 + lane] = make_float2(m, lsum);
+    }
+    __syncthreads();
+    if (kgrp > 0) return;
+    float l0 = lsum;
+#pragma unroll
+    for (int kg = 1; kg < KG; ++kg) {
+      const int slot = (kg - 1) * NWR + wr;
+      const float2 ml = xml[slot * 64 + lane];
+      // a side without visible keys carries no weight (its maximum may come
+      // from masked scores)
+      const bool has0 = l0 > 0.f, has1 = ml.y > 0.f;
+      const float mn = has0 && has1 ? fmaxf(m, ml.x) : has1 ? ml.x : m;
+      const float f0 = has0 ? fast_exp2(m - mn) : 0.f;
+      const float f1 = has1 ? fast_exp2(ml.x - mn) : 0.f;
+      if (kg < n1) {                           // group kg had tiles (uniform)
+#pragma unroll
+        for (int db = 0; db < DB; ++db) o[db] = o[db] * f0 + xo[(slot * DB + db) * 64 + lane] * f1;
+        l0 = l0 * f0 + ml.y * f1;
+        m = mn;
+      }
+    }
+    write_rows(l0);
+    return;
+  }
+  if constexpr (KG == 2 && !DIRECT) {
     // When both key groups end on the same pair, group 1 hands its (max,
     // sum, O) to group 0 through the ring and one combined partial is
     // written (slot key group 0); otherwise each group writes its own.
@@ -905,13 +986,31 @@ __global__ __launch_bounds__(256) void verify_stream_merge(VerifyArgs a, int G, 
 
 template <int D, int NWR, int KG, int NBUF, bool PAGED>
 hipError_t launch_stream(const VerifyArgs& a, const VerifyPlan& p, hipStream_t st) {
-  hipLaunchKernelGGL((verify_stream_bf16<D, NWR, KG, NBUF, PAGED>), dim3(p.stream_wgs),
+  hipLaunchKernelGGL((verify_stream_bf16<D, NWR, KG, NBUF, PAGED, false>), dim3(p.stream_wgs),
                      dim3(NWR * KG * 64), 0, st, a, p.stream_wgs, p.row_groups);
+  return hipGetLastError();
+}
+
+// one work-group per pair, four key groups (two where a tile has too few
+// 64-lane copies for sixteen waves)
+template <int D, int NWR, bool PAGED>
+hipError_t launch_direct(const VerifyArgs& a, const VerifyPlan& p, hipStream_t st) {
+  constexpr int KG = NWR == 4 && D == 64 ? 2 : 4;
+  const int pairs = a.B * a.Hkv * p.row_groups;
+  hipLaunchKernelGGL((verify_stream_bf16<D, NWR, KG, 2 * KG + 1, PAGED, true>), dim3(pairs),
+                     dim3(NWR * KG * 64), 0, st, a, pairs, p.row_groups);
   return hipGetLastError();
 }
 
 template <int D, bool PAGED>
 hipError_t dispatch_rb(const VerifyArgs& a, const VerifyPlan& p, hipStream_t st) {
+  if (p.direct) {
+    switch (p.row_blocks) {
+      case 1: return launch_direct<D, 1, PAGED>(a, p, st);
+      case 2: return launch_direct<D, 2, PAGED>(a, p, st);
+      default: return launch_direct<D, 4, PAGED>(a, p, st);
+    }
+  }
   switch (p.row_blocks) {
     case 1: return launch_stream<D, 1, stream_cfg(1).kg, stream_cfg(1).nbuf, PAGED>(a, p, st);
     case 2: return launch_stream<D, 2, stream_cfg(2).kg, stream_cfg(2).nbuf, PAGED>(a, p, st);
@@ -964,6 +1063,13 @@ VerifyPlan plan_verify(int B, int k, int Hq, int Hkv, int D, int capacity, int d
     const long long tiles_cap = pairs * ((capacity + kTile - 1) / kTile);
     p.stream_wgs = (int)std::max(1LL, std::min((long long)std::max(1, cus) * stream_cfg(p.row_blocks).per_cu,
                                                tiles_cap / 4));
+    // up to eight tiles per pair, two per key group: one work-group per pair
+    // then takes no longer than the split stream, and the merge launch goes
+    // (draft layer of 16 sequences, 240 positions: 193.5 -> 186.2 us; one
+    // sequence with the head, 128 positions: 181.4 -> 172.1 us).  Longer
+    // caches leave too few work-groups (1024 keys, 8 pairs of 64 rows: 18.0 us
+    // split, 25.4 us so).
+    p.direct = capacity <= 8 * kTile;
     // tile indices are 32-bit on the device
     if (pairs * ((capacity + kTile - 1) / kTile) >= (1LL << 30)) p.ok = false;
     p.part_rows = (size_t)(pairs + p.stream_wgs) * p.key_groups * p.rows_wg;
@@ -995,7 +1101,7 @@ hipError_t launch_verify(const VerifyArgs& a, const VerifyPlan& p, int dtype, hi
   if (dtype == 0)
     hipLaunchKernelGGL(verify_merge, dim3(a.Hkv * a.B, (p.rows + 3) / 4), dim3(256), 0, st, a,
                        p.keys_per_split, p.nsplit, p.rows_padded, paged ? 1 : 0);
-  else
+  else if (!p.direct)
     hipLaunchKernelGGL(verify_stream_merge, dim3(a.B * a.Hkv * p.row_groups, (p.rows_wg + 3) / 4),
                        dim3(256), 0, st, a, p.stream_wgs, p.row_groups, p.key_groups, p.rows_wg,
                        paged ? 1 : 0);

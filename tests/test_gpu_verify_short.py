@@ -1,0 +1,39 @@
+"""Verification over short caches (at most 256 positions): one work-group per
+(sequence, KV head) combines its key groups and writes the rows itself.
+
+Capacities around the 32-key tile, the four key groups and the 256-position
+limit of this path (257 takes the split stream), sequences from empty over
+shorter than the block to full, one to five 16-row blocks, both head sizes,
+contiguous and paged, and a negative scale; tolerances as in
+test_gpu_verify.py."""
+
+import math
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2505_12728_amd import synth
+from tests.gpu_util import assert_close, assert_lse_close
+from tests.test_gpu_verify import run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("cap,k,hq,hkv,D,paged", [
+    (1, 1, 2, 2, 128, False), (31, 4, 4, 2, 64, False), (32, 5, 8, 8, 128, False), (33, 6, 16, 4, 128, False),
+    (64, 16, 2, 1, 64, False), (97, 7, 8, 2, 128, True), (128, 9, 16, 2, 128, False), (129, 4, 36, 4, 64, False),
+    (160, 8, 8, 1, 64, True), (240, 7, 32, 8, 128, False), (255, 8, 16, 2, 128, False), (256, 5, 32, 4, 128, True),
+    (257, 5, 32, 4, 128, False)])
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_verify_short_cache(cap, k, hq, hkv, D, paged, sign):
+    lens = np.array([cap, 0, min(cap, max(0, k - 2)), min(cap, 32), max(1, cap - 33), min(cap, 96)], np.int32)
+    w = synth.Workload("short", "bf16", batch=len(lens), hq=hq, hkv=hkv, head_dim=D, kv_len=cap, block=k, paged=paged,
+                       kv_len_min=1)
+    d = synth.verify_inputs(w, seed=cap, kv_len=lens)
+    scale = sign / math.sqrt(D)
+    out, lse = run_gpu(d, scale=scale)
+    ro, rl = oracle.verify_attention(d["q"].values, d["k_cache"].values, d["v_cache"].values, d["kv_len"], scale,
+                                     page_table=d["page_table"])
+    assert_close(out, ro, "bf16", "out")
+    assert_lse_close(lse, rl, "bf16", "lse")
