@@ -127,6 +127,21 @@ struct CompressLds {
   unsigned char stage[IN8 ? 4 : 1][IN8 ? 64 * DH : 16];    // int8 staging tiles
   int8_t sexp[IN8 ? kQ8MaxSplit : 4];                      // int8: the split's token exponents
 };
+// int8 input, up to four waves: the fp16 ring holds the tile of P V, that of the scores and
+// the one being converted, the staging ring the tile being converted and
+// the one in flight, so three and two slots are enough: 80 KB with the
+// exponents, two work-groups per compute unit where four slots of each held
+// one (16 sequences of 1024 tokens, 128 latents, 32 heads: 61.9 -> 48.1 us; 7
+// of 3001, 70 latents, 64 heads: 128.6 -> 100.0 us).
+template <int DH>
+struct CompressLdsQ8Small {
+  unsigned char ring[3][64 * DH * 2];                       // fp16 tiles
+  unsigned char stage[2][64 * DH];                          // int8 staging tiles
+  int8_t sexp[kQ8MaxSplit];                                 // the split's token exponents
+};
+template <int DH> struct CompressLds<1, DH, true> : CompressLdsQ8Small<DH> {};
+template <int DH> struct CompressLds<2, DH, true> : CompressLdsQ8Small<DH> {};
+template <int DH> struct CompressLds<4, DH, true> : CompressLdsQ8Small<DH> {};
 
 // The matrix-core pass of a work-group (NW waves x 32 latents of one
 // (sequence, head), one token split).  Returns, per thread, the range flags
@@ -147,7 +162,10 @@ __device__ __forceinline__ unsigned compress_pass(const CompressArgs a, int n_bh
   constexpr int DMA = IN_PIECES / 64;       // 64-lane copies per tile
   constexpr int DMA_PER_WAVE = DMA / NW;
   constexpr int CVT_PER_THREAD = IN_PIECES / (NW * 64);   // input pieces converted per thread
-  constexpr int NBUF = 4;
+  constexpr bool SMALL8 = IN8 && NW <= 4;
+  constexpr int NBUF = SMALL8 ? 3 : 4;      // ring slots
+  constexpr int NIN = SMALL8 ? 2 : 4;       // slots of the copies' ring (bf16: the ring itself)
+  constexpr int UNROLL = SMALL8 ? 6 : 4;    // steps after which both repeat
   constexpr float kRescale = 15.f;      // P = exp2(s - m) <= 2^15 < the fp16 maximum
   static_assert(DMA % NW == 0 && IN_PIECES % (NW * 64) == 0, "tile work must split evenly");
   static_assert(!IN8 || DH == 128, "int8 input: 128-channel heads");
@@ -163,7 +181,7 @@ __device__ __forceinline__ unsigned compress_pass(const CompressArgs a, int n_bh
   auto& stage = sm.stage;
   auto& sexp = sm.sexp;
   static_assert(sizeof(sm.ring[0]) == TILE_BYTES, "ring slot size");
-  static_assert(!CM || (CVT_PER_THREAD == 2 && sizeof(sm.tr[0]) == TILE_BYTES), "channel-major copy: two pieces per thread");
+  static_assert(!CM || CVT_PER_THREAD == 2, "channel-major copy: two pieces per thread");
 
   int bh, lt;
   map_tile(blockIdx.x, n_bh, n_lt, bh, lt);
@@ -369,7 +387,8 @@ __device__ __forceinline__ unsigned compress_pass(const CompressArgs a, int n_bh
   }
   // CM: P V fragments at the lane's offset in the channel-major copy; the
   // half and the value block are immediate offsets
-  const uint32_t cm_v = CM ? lds_addr(sm.tr[0]) + lane * 16 : 0u;
+  uint32_t cm_v = 0u;
+  if constexpr (CM) cm_v = lds_addr(sm.tr[0]) + lane * 16;
   // this thread's conversion pieces: base of its input (ring or staging)
   constexpr int IN_TILE = IN8 ? TT * DH : TILE_BYTES;    // input slot bytes
   const uint32_t cvt_base = (IN8 ? lds_addr(stage[0]) : ring0) + tid * 16;
@@ -531,10 +550,17 @@ __device__ __forceinline__ unsigned compress_pass(const CompressArgs a, int n_bh
   constexpr int KPG = 4 / NQK;         // 16-token blocks per QK group
   issue(0, 0);
   issue(min(1, last), 1);
-  issue(min(2, last), 2);
-  wait_vm_then_barrier<2 * DMA_PER_WAVE>();           // tile 0 landed
-  convert(0, 0);
-  wait_vm_then_barrier<DMA_PER_WAVE>();               // tile 1 landed, tile 0 converted
+  if constexpr (SMALL8) {
+    wait_vm_then_barrier<DMA_PER_WAVE>();             // tile 0 landed
+    convert(0, 0);
+    wait_vm_then_barrier<0>();                        // tile 1 landed, tile 0 converted
+    issue(min(2, last), 0);
+  } else {
+    issue(min(2, last), 2);
+    wait_vm_then_barrier<2 * DMA_PER_WAVE>();         // tile 0 landed
+    convert(0, 0);
+    wait_vm_then_barrier<DMA_PER_WAVE>();             // tile 1 landed, tile 0 converted
+  }
   convert(1, 1);
   floatx4 scur[4][2];
   {
@@ -651,18 +677,18 @@ __device__ __forceinline__ unsigned compress_pass(const CompressArgs a, int n_bh
   // and (kRot) the first group's reads done.
   auto step = [&](int it, auto mask_tag, auto ph_tag) {
     constexpr int PH = decltype(ph_tag)::value;
-    // offset of the slot of tile it + K in a ring of slots of SZ bytes
-    auto slot = [&](auto k_tag, auto sz_tag) {
-      constexpr int K = decltype(k_tag)::value, SZ = decltype(sz_tag)::value;
+    // offset of the slot of tile it + K in a ring of NS slots of SZ bytes
+    auto slot = [&](auto k_tag, auto ns_tag, auto sz_tag) {
+      constexpr int K = decltype(k_tag)::value, NS = decltype(ns_tag)::value, SZ = decltype(sz_tag)::value;
       if constexpr (PH >= 0)
-        return CtOff<((PH + K) % NBUF) * SZ>{};
+        return CtOff<((PH + K) % NS) * SZ>{};
       else
-        return (uint32_t)(((it + K) % NBUF) * SZ);
+        return (uint32_t)(((it + K) % NS) * SZ);
     };
-    const auto nb = slot(CtOff<1>{}, CtOff<TILE_BYTES>{});        // scores of tile it+1
-    const auto cs = slot(CtOff<2>{}, CtOff<TILE_BYTES>{});        // converted tile it+2
-    const auto ci = slot(CtOff<2>{}, CtOff<IN_TILE>{});           // its input
-    const auto vb = slot(CtOff<0>{}, CtOff<TILE_BYTES>{});        // P V of tile it
+    const auto nb = slot(CtOff<1>{}, CtOff<NBUF>{}, CtOff<TILE_BYTES>{});   // scores of tile it+1
+    const auto cs = slot(CtOff<2>{}, CtOff<NBUF>{}, CtOff<TILE_BYTES>{});   // converted tile it+2
+    const auto ci = slot(CtOff<2>{}, CtOff<NIN>{}, CtOff<IN_TILE>{});       // its input
+    const auto vb = slot(CtOff<0>{}, CtOff<NBUF>{}, CtOff<TILE_BYTES>{});   // P V of tile it
     const uint32_t cb = lds_addr(ring[(it + 2) % NBUF]);          // int8: converted tile, absolute
     u32x2 vr[2][4][2];
     u32x4 cv[CVT_PER_THREAD];
@@ -674,7 +700,7 @@ __device__ __forceinline__ unsigned compress_pass(const CompressArgs a, int n_bh
       // tile it+2 landed; tile it+1 converted by every wave; buffer it-1 free
       wait_vm_then_barrier<0>();
       reads(std::integral_constant<int, 0>{}, nb, vb, ci, xr, vr, cv, ce, it + 2, std::false_type{});
-      issue(min(it + 3, last), (it + 3) % NBUF);
+      issue(min(it + 3, last), (it + 3) % NIN);
     }
     static_for<0, NG>([&](auto gtag) {
       constexpr int g = decltype(gtag)::value;
@@ -696,7 +722,7 @@ __device__ __forceinline__ unsigned compress_pass(const CompressArgs a, int n_bh
         wait_vm_then_barrier<0>();
         if constexpr (!decltype(mask_tag)::value) {
           reads(std::integral_constant<int, 0>{}, cs, vb, ci, xr, vr, cv, ce, it + 2, std::false_type{});
-          issue(min(it + 4, last), it % NBUF);
+          issue(min(it + 4, last), it % NIN);
         }
       }
       if constexpr (g == NQK + NPVH) {
@@ -803,17 +829,13 @@ __device__ __forceinline__ unsigned compress_pass(const CompressArgs a, int n_bh
     int ce0[CVT_PER_THREAD];
     const auto nb0 = CtOff<TILE_BYTES>{};        // ring slot 1
     reads(std::integral_constant<int, 0>{}, nb0, nb0, nb0, xr, vr0, cv0, ce0, 0, std::false_type{});
-    issue(min(3, last), 3 % NBUF);
+    issue(min(3, last), 3 % NIN);
     lds_wait();
     reads(std::integral_constant<int, 0>{}, nb0, nb0, nb0, xr, vr0, cv0, ce0, 0, std::true_type{});
   }
   int it = 0;
-  for (; it + NBUF < last; it += NBUF) {
-    step(it, std::false_type{}, CtOff<0>{});
-    step(it + 1, std::false_type{}, CtOff<1>{});
-    step(it + 2, std::false_type{}, CtOff<2>{});
-    step(it + 3, std::false_type{}, CtOff<3>{});
-  }
+  for (; it + UNROLL < last; it += UNROLL)
+    static_for<0, UNROLL>([&](auto ph) { step(it + decltype(ph)::value, std::false_type{}, ph); });
   for (; it + 1 < last; ++it) step(it, std::false_type{}, CtOff<-1>{});
   if (last >= 1) step(last - 1, std::true_type{}, CtOff<-1>{});
   {
@@ -1224,9 +1246,11 @@ CompressPlan plan_compress(int B, int N, int C, int d, int H, int dtype, int cus
     p.lat_tile = waves * 32;
     p.lat_tiles = (C + p.lat_tile - 1) / p.lat_tile;
     // split the tokens so that the grid fills the device in one round:
-    // two work-groups per compute unit (one of eight waves, or with int8
-    // input, whose staging ring doubles the LDS), keeping at least 128
-    // tokens per split; int8 splits hold at most kQ8MaxSplit tokens
+    // two work-groups per compute unit (one of eight waves, and one with int8
+    // input, where two would mostly buy a merge launch: 5 sequences of 638
+    // tokens, 67 latents, 32 heads 20.2 us in one split, 27.6 us in three),
+    // keeping at least 128 tokens per split; int8 splits hold at most
+    // kQ8MaxSplit tokens
     const long long groups = n_bh * p.lat_tiles;
     const long long resident = (long long)std::max(cus, 1) * (waves == 8 || dtype == kCompressInt8 ? 1 : 2);
     long long nsplit = std::max(1LL, resident / groups);
