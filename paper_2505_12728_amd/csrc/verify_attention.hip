@@ -47,12 +47,17 @@ constexpr int kTile = 32;       // keys per tile of the bf16 kernel
 
 // bf16 stream kernel configuration by 16-row blocks per work-group (1, 2
 // or 4): key groups (waves = blocks x key groups), ring slots of one tile
-// (16 KB for D = 128) and work-groups per compute unit
+// (16 KB for D = 128) and work-groups per compute unit.  A single block
+// takes two key groups while a work-group has few tiles (kFewTiles): its
+// tiles are a serial chain of one wave otherwise (one sequence, 32 heads,
+// 1200 keys: 17.1 -> 14.6 us; 3000 keys: 21.5 -> 19.8 us).  With many tiles
+// the second wave gives nothing (60000 keys, 8 heads: 62.4 -> 63.9 us).
 struct StreamCfg {
   int kg, nbuf, per_cu;
 };
-constexpr StreamCfg stream_cfg(int row_blocks) {
-  return row_blocks == 4 ? StreamCfg{2, 8, 1} : StreamCfg{1, 4, 2};
+constexpr int kFewTiles = 24;
+constexpr StreamCfg stream_cfg(int row_blocks, int few) {
+  return row_blocks == 4 ? StreamCfg{2, 8, 1} : row_blocks == 1 && few ? StreamCfg{2, 5, 2} : StreamCfg{1, 4, 2};
 }
 
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short shortx4;
@@ -1012,9 +1017,11 @@ hipError_t dispatch_rb(const VerifyArgs& a, const VerifyPlan& p, hipStream_t st)
     }
   }
   switch (p.row_blocks) {
-    case 1: return launch_stream<D, 1, stream_cfg(1).kg, stream_cfg(1).nbuf, PAGED>(a, p, st);
-    case 2: return launch_stream<D, 2, stream_cfg(2).kg, stream_cfg(2).nbuf, PAGED>(a, p, st);
-    default: return launch_stream<D, 4, stream_cfg(4).kg, stream_cfg(4).nbuf, PAGED>(a, p, st);
+    case 1:
+      if (p.key_groups == 2) return launch_stream<D, 1, 2, stream_cfg(1, 1).nbuf, PAGED>(a, p, st);
+      return launch_stream<D, 1, 1, stream_cfg(1, 0).nbuf, PAGED>(a, p, st);
+    case 2: return launch_stream<D, 2, stream_cfg(2, 0).kg, stream_cfg(2, 0).nbuf, PAGED>(a, p, st);
+    default: return launch_stream<D, 4, stream_cfg(4, 0).kg, stream_cfg(4, 0).nbuf, PAGED>(a, p, st);
   }
 }
 
@@ -1057,12 +1064,13 @@ VerifyPlan plan_verify(int B, int k, int Hq, int Hkv, int D, int capacity, int d
     p.row_groups = (blocks16 + p.row_blocks - 1) / p.row_blocks;
     p.rows_wg = p.row_blocks * 16;
     p.rows_padded = p.row_groups * p.rows_wg;
-    p.key_groups = stream_cfg(p.row_blocks).kg;
     const long long pairs = (long long)B * Hkv * p.row_groups;
     // at least 4 tiles per work-group when every sequence is at capacity
     const long long tiles_cap = pairs * ((capacity + kTile - 1) / kTile);
-    p.stream_wgs = (int)std::max(1LL, std::min((long long)std::max(1, cus) * stream_cfg(p.row_blocks).per_cu,
+    // (two work-groups per unit in either configuration of a single block)
+    p.stream_wgs = (int)std::max(1LL, std::min((long long)std::max(1, cus) * stream_cfg(p.row_blocks, 0).per_cu,
                                                tiles_cap / 4));
+    p.key_groups = stream_cfg(p.row_blocks, tiles_cap <= (long long)kFewTiles * p.stream_wgs).kg;
     // up to eight tiles per pair, two per key group: one work-group per pair
     // then takes no longer than the split stream, and the merge launch goes
     // (draft layer of 16 sequences, 240 positions: 193.5 -> 186.2 us; one

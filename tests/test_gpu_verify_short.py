@@ -37,3 +37,21 @@ def test_verify_short_cache(cap, k, hq, hkv, D, paged, sign):
                                      page_table=d["page_table"])
     assert_close(out, ro, "bf16", "out")
     assert_lse_close(lse, rl, "bf16", "lse")
+
+
+@pytest.mark.parametrize("kv,k,hq,hkv,D,B,paged", [
+    (257, 5, 8, 8, 128, 1, False), (300, 16, 2, 2, 64, 3, True), (1201, 5, 32, 32, 128, 1, False),
+    (2999, 4, 8, 2, 128, 2, True), (1500, 8, 4, 2, 64, 5, False)])
+def test_verify_one_row_block_few_tiles(kv, k, hq, hkv, D, B, paged):
+    # at most 16 query rows per KV head and few tiles per work-group: two key
+    # groups per work-group, ragged lengths with empty and very short ones
+    lens = np.array([kv, 33, 0, max(1, k - 1), kv - 17][:B], np.int32)
+    w = synth.Workload("few", "bf16", batch=B, hq=hq, hkv=hkv, head_dim=D, kv_len=kv, block=k, paged=paged,
+                       kv_len_min=1)
+    d = synth.verify_inputs(w, seed=kv, kv_len=lens)
+    scale = 1.0 / math.sqrt(D)
+    out, lse = run_gpu(d, scale=scale)
+    ro, rl = oracle.verify_attention(d["q"].values, d["k_cache"].values, d["v_cache"].values, d["kv_len"], scale,
+                                     page_table=d["page_table"])
+    assert_close(out, ro, "bf16", "out")
+    assert_lse_close(lse, rl, "bf16", "lse")
