@@ -120,6 +120,36 @@ __device__ __forceinline__ float split_sum(const float* part, int ksplit, size_t
   return s;
 }
 
+// The same for four consecutive values at a 16-byte aligned index, added in
+// the same order: every split's load is issued before the first is used
+// (one after the other they cost a memory latency each).
+template <int M>
+__device__ __forceinline__ void split_sum4(const float* part, int ksplit, size_t stride, const size_t (&idx)[M],
+                                           floatx4 (&s)[M]) {
+  floatx4 v[M][kLinearMaxSplits];
+#pragma unroll
+  for (int ks = 0; ks < kLinearMaxSplits; ++ks)
+    if (ks < ksplit) {
+#pragma unroll
+      for (int i = 0; i < M; ++i) v[i][ks] = *reinterpret_cast<const floatx4*>(part + ks * stride + idx[i]);
+    }
+#pragma unroll
+  for (int i = 0; i < M; ++i) s[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int ks = 0; ks < kLinearMaxSplits; ++ks)
+    if (ks < ksplit) {
+#pragma unroll
+      for (int i = 0; i < M; ++i) s[i] += v[i][ks];
+    }
+}
+
+__device__ __forceinline__ void store_bf16x4(__bf16* dst, const floatx4& v) {
+  Pack8 pk;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) pk.b[e] = float_to_bf16(v[e]);
+  *reinterpret_cast<u32x2*>(dst) = u32x2{pk.u[0], pk.u[1]};
+}
+
 __device__ __forceinline__ float block_sum(float v, float* red) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -195,15 +225,24 @@ __global__ __launch_bounds__(kEpiThreads) void epi_add_cols(const float* part, i
 }
 
 // 1 / sqrt(mean(y^2) + eps) of row r of width d from epi_add_cols' nblk block
-// sums (added in block order).
+// sums (added in block order, eight loads in flight).
 __device__ __forceinline__ float row_scale(const float* ss, int nblk, int r, int d, float eps) {
   float t = 0.f;
-  for (int i = 0; i < nblk; ++i) t += ss[(size_t)r * nblk + i];
+  for (int i0 = 0; i0 < nblk; i0 += 8) {
+    float v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = i0 + i < nblk ? ss[(size_t)r * nblk + i0 + i] : 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) t += v[i];
+  }
   return 1.f / sqrtf(t / (float)d + eps);
 }
 // A row whose mean square overflows has scale 0: its normalised values are 0
 // even where the unscaled projection overflowed.
 __device__ __forceinline__ float scaled(float x, float inv) { return inv == 0.f ? 0.f : x * inv; }
+__device__ __forceinline__ floatx4 scaled(const floatx4& x, float inv) {
+  return floatx4{scaled(x[0], inv), scaled(x[1], inv), scaled(x[2], inv), scaled(x[3], inv)};
+}
 
 static int epi_blocks(int N) { return (N + kEpiCols - 1) / kEpiCols; }
 
@@ -240,30 +279,39 @@ __global__ __launch_bounds__(kEpiThreads) void epi_rope_qkv(const float* part, i
     rot[threadIdx.x] = make_float2(cs, sn);
   }
   __syncthreads();
-  // thread t of the row: pair t (query and key heads), then value element
-  // t - pairs
-  const int pairs = (Hq + Hkv) * half;
+  // thread t of the row: pairs 4 t .. 4 t + 3 (query and key heads), then
+  // four value elements (D is a multiple of 64, so both stay in one head)
+  const int quads = (Hq + Hkv) * half / 4;
   const int t = blockIdx.x * kEpiThreads + threadIdx.x;
-  if (t < pairs) {
-    const int hh = t / half, i = t - hh * half;
-    const size_t base = (size_t)r * N + (size_t)hh * D;
-    const float x0 = scaled(split_sum(part, ksplit, stride, base + i), inv);
-    const float x1 = scaled(split_sum(part, ksplit, stride, base + i + half), inv);
-    const float cs = rot[i].x, sn = rot[i].y;
-    const float y0 = x0 * cs - x1 * sn, y1 = x1 * cs + x0 * sn;
-    if (hh < Hq) {
-      __bf16* dst = q + ((size_t)r * Hq + hh) * D;
-      dst[i] = float_to_bf16(y0);
-      dst[i + half] = float_to_bf16(y1);
-    } else if (store) {
-      __bf16* dst = kc + (((size_t)b * Lmax + p) * Hkv + (hh - Hq)) * D;
-      dst[i] = float_to_bf16(y0);
-      dst[i + half] = float_to_bf16(y1);
+  if (t < quads) {
+    const int hh = t * 4 / half, i = t * 4 - hh * half;
+    const size_t base = (size_t)r * N + (size_t)hh * D + i;
+    const size_t idx[2] = {base, base + half};
+    floatx4 x[2];
+    split_sum4(part, ksplit, stride, idx, x);
+    const floatx4 x0 = scaled(x[0], inv), x1 = scaled(x[1], inv);
+    floatx4 y0, y1;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float cs = rot[i + e].x, sn = rot[i + e].y;
+      y0[e] = x0[e] * cs - x1[e] * sn;
+      y1[e] = x1[e] * cs + x0[e] * sn;
     }
-  } else if (store && t < pairs + Hkv * D) {
-    const int hv = (t - pairs) / D, e = (t - pairs) - hv * D;
-    const float v = scaled(split_sum(part, ksplit, stride, (size_t)r * N + (size_t)(Hq + Hkv + hv) * D + e), inv);
-    vc[(((size_t)b * Lmax + p) * Hkv + hv) * D + e] = float_to_bf16(v);
+    if (hh < Hq) {
+      __bf16* dst = q + ((size_t)r * Hq + hh) * D + i;
+      store_bf16x4(dst, y0);
+      store_bf16x4(dst + half, y1);
+    } else if (store) {
+      __bf16* dst = kc + (((size_t)b * Lmax + p) * Hkv + (hh - Hq)) * D + i;
+      store_bf16x4(dst, y0);
+      store_bf16x4(dst + half, y1);
+    }
+  } else if (store && t < quads + Hkv * D / 4) {
+    const int e4 = (t - quads) * 4;               // element of the row's value heads
+    const size_t idx[1] = {(size_t)r * N + (size_t)(Hq + Hkv) * D + e4};
+    floatx4 v[1];
+    split_sum4(part, ksplit, stride, idx, v);
+    store_bf16x4(vc + ((size_t)b * Lmax + p) * Hkv * D + e4, scaled(v[0], inv));
   }
 }
 
@@ -272,14 +320,19 @@ __global__ __launch_bounds__(kEpiThreads) void epi_rope_qkv(const float* part, i
 __global__ __launch_bounds__(kEpiThreads) void epi_swiglu(const float* part, int ksplit, int R, int I,
                                                           __bf16* act, const float* ss, int nblk, int d, float eps) {
   const int r = blockIdx.y;
-  const int i = blockIdx.x * kEpiThreads + threadIdx.x;
+  const int i = (blockIdx.x * kEpiThreads + threadIdx.x) * 4;   // I is a multiple of 256
   if (i >= I) return;
   const size_t N = 2 * (size_t)I;
-  const size_t stride = (size_t)R * N;
+  const size_t idx[2] = {(size_t)r * N + i, (size_t)r * N + I + i};
+  floatx4 x[2], y;
+  split_sum4(part, ksplit, (size_t)R * N, idx, x);
   const float inv = row_scale(ss, nblk, r, d, eps);
-  const float g = scaled(split_sum(part, ksplit, stride, (size_t)r * N + i), inv);
-  const float u = scaled(split_sum(part, ksplit, stride, (size_t)r * N + I + i), inv);
-  act[(size_t)r * I + i] = float_to_bf16(g / (1.f + expf(-g)) * u);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float g = scaled(x[0][e], inv), u = scaled(x[1][e], inv);
+    y[e] = g / (1.f + expf(-g)) * u;
+  }
+  store_bf16x4(act + (size_t)r * I + i, y);
 }
 
 // ------------------------------------------------- K drafts in K / k' passes
@@ -456,7 +509,7 @@ hipError_t launch_semi_ar(const SemiArArgs& a, const SemiArPlan& p, hipStream_t 
                      (const float*)nullptr, x0, a.ln1, h, ss);
   // q, k, v with RoPE; k, v appended to the cache
   if ((e = lin(h, a.wqkv, a.wqkv_s, d, nqkv, p.qkv)) != hipSuccess) return e;
-  const int rope_threads = (a.Hq + a.Hkv) * (D / 2) + a.Hkv * D;
+  const int rope_threads = ((a.Hq + a.Hkv) * (D / 2) + a.Hkv * D) / 4;
   hipLaunchKernelGGL(epi_rope_qkv, dim3((rope_threads + kEpiThreads - 1) / kEpiThreads, R), dim3(kEpiThreads), 0, st, part, p.qkv.ksplit, R, nqkv, a.pos, a.r,
                      a.Hq, a.Hkv, D, log((double)a.theta), a.Lmax, q,
                      static_cast<__bf16*>(a.k_cache), static_cast<__bf16*>(a.v_cache), kv_len, ss, (int)eg.x, d, a.eps);
@@ -488,7 +541,7 @@ hipError_t launch_semi_ar(const SemiArArgs& a, const SemiArPlan& p, hipStream_t 
                      (const float*)nullptr, x0, x1, a.ln2, h, ss);
   // act = SwiGLU(h), out = x1 + act Wdown^T
   if ((e = lin(h, a.wgu, a.wgu_s, d, 2 * a.I, p.gu)) != hipSuccess) return e;
-  hipLaunchKernelGGL(epi_swiglu, dim3((a.I + kEpiThreads - 1) / kEpiThreads, R), dim3(kEpiThreads), 0, st, part,
+  hipLaunchKernelGGL(epi_swiglu, dim3((a.I / 4 + kEpiThreads - 1) / kEpiThreads, R), dim3(kEpiThreads), 0, st, part,
                      p.gu.ksplit, R, a.I, act, ss, (int)eg.x, d, a.eps);
   if ((e = lin(act, a.wdown, a.wdown_s, a.I, d, p.down)) != hipSuccess) return e;
   return launch_epi_add(part, p.down.ksplit, R, d, nullptr, x1, a.out, st);
