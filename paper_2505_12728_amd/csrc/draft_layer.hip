@@ -47,6 +47,7 @@ struct LinearCfg {
   static constexpr int NW = kLinearMaxUnits * (2 / CB) + (CB == 1 ? 2 : 1);   // 8 or 16 waves
 };
 constexpr int kEpiThreads = 256;
+typedef floatx4 floatx4_u __attribute__((aligned(4)));   // four floats at any float's alignment
 
 // part[ks][r][n] = sum over split ks's chunks of x[r][k] w[n][k], for the
 // rows r0 .. r0 + 16 RB - 1 of this pass.  Q8: the weight holds int8 rows
@@ -81,10 +82,15 @@ __global__ __launch_bounds__((LinearCfg<RB, Q8>::NW * 64)) void linear_partial(L
   for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) acc[cb][rb] = floatx4{0.f, 0.f, 0.f, 0.f};
-  if (ch0 < ch1)
-    stream_product<RB, CB, NW, Q8>(static_cast<const unsigned char*>(a.w) + (size_t)n0 * K * (Q8 ? 1 : 2), N - n0,
-                                     active, static_cast<const uint16_t*>(a.x) + (size_t)r0 * K, min(R - r0, RB * 16),
-                                     K, ch0, ch1, rot, ring, acc);
+  if (ch0 < ch1) {
+    const size_t row_bytes = (size_t)K * (Q8 ? 1 : 2);
+    int valid[CB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) valid[cb] = N - n0 - 16 * cb;
+    stream_product<RB, CB, NW, Q8>(static_cast<const unsigned char*>(a.w) + n0 * row_bytes, 16 * row_bytes, valid,
+                                   active, static_cast<const uint16_t*>(a.x) + (size_t)r0 * K, min(R - r0, RB * 16),
+                                   K, ch0, ch1, rot, ring, acc);
+  }
   if (!active) return;
   // accumulator element i of lane (c, G): input row rb*16 + c, column n0 +
   // 16 cb + 4G + i
@@ -335,6 +341,90 @@ __global__ __launch_bounds__(kEpiThreads) void epi_swiglu(const float* part, int
   store_bf16x4(act + (size_t)r * I + i, y);
 }
 
+// The gate / up projection with SwiGLU as its epilogue, for the whole
+// reduction in one split: act[r][i] = silu(g) * u, bf16, g and u the products
+// with weight rows i and I + i times the row's norm factor.  A unit is 16
+// gate rows and their 16 up rows: the two blocks of a wave, or two waves
+// that meet through LDS (the waves of int8 rows, see LinearCfg).  Same bits
+// as linear_partial and epi_swiglu, without the partials' way through memory
+// and the second launch.
+struct SwigluArgs {
+  __bf16* act;
+  const float* ss;
+  int nblk, d, I, units;   // units per work-group
+  float eps;
+};
+template <int RB, bool Q8>
+__global__ __launch_bounds__((LinearCfg<RB, Q8>::NW * 64)) void linear_swiglu(LinearArgs a, SwigluArgs g) {
+  constexpr int NW = LinearCfg<RB, Q8>::NW, CB = LinearCfg<RB, Q8>::CB;
+  __shared__ __align__(16) unsigned char ring[stream_ring_bytes(RB)];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), G = lane >> 4, c = lane & 15;
+  const int unit = CB == 2 ? w : w >> 1, up = CB == 2 ? 0 : w & 1;
+  const int p0 = (blockIdx.x * g.units + unit) * 16;
+  const int r0 = blockIdx.z * RB * 16;
+  const int K = a.K, I = g.I, R = a.R;
+  const int nch = K / kStreamChunk;
+  const int rot = (int)((blockIdx.x >> 3) % (unsigned)nch);
+  const bool active = w < NW - 1 && unit < g.units && p0 < I;   // wave-uniform
+  floatx4 acc[CB][RB];
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) acc[cb][rb] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const size_t row_bytes = (size_t)K * (Q8 ? 1 : 2);
+  int valid[CB];
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) valid[cb] = I - p0;
+  stream_product<RB, CB, NW, Q8>(static_cast<const unsigned char*>(a.w) + (p0 + (size_t)up * I) * row_bytes,
+                                 I * row_bytes, valid, active, static_cast<const uint16_t*>(a.x) + (size_t)r0 * K,
+                                 min(R - r0, RB * 16), K, 0, nch, rot, ring, acc);
+  const int n = p0 + 4 * G;
+  if constexpr (Q8) {
+    if (active) {
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) {
+        const floatx4 sc = *reinterpret_cast<const floatx4_u*>(a.wscale + (size_t)(up + cb) * I + n);
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) acc[cb][rb] *= sc;
+      }
+    }
+  }
+  floatx4 uv[RB];
+  if constexpr (CB == 2) {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) uv[rb] = acc[1][rb];
+  } else {
+    // every wave is done with the ring: the up products go through it
+    floatx4* xu = reinterpret_cast<floatx4*>(ring);
+    static_assert(kLinearMaxUnits * RB * 1024 <= stream_ring_bytes(RB), "up products fit the ring");
+    __syncthreads();
+    if (active && up) {
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) xu[(unit * RB + rb) * 64 + lane] = acc[0][rb];
+    }
+    __syncthreads();
+    if (active && !up) {
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) uv[rb] = xu[(unit * RB + rb) * 64 + lane];
+    }
+  }
+  if (!active || up) return;
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const int r = r0 + rb * 16 + c;
+    if (r >= R) continue;
+    const float inv = row_scale(g.ss, g.nblk, r, g.d, g.eps);
+    floatx4 y;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float gv = scaled(acc[0][rb][e], inv), u = scaled(uv[rb][e], inv);
+      y[e] = gv / (1.f + expf(-gv)) * u;
+    }
+    store_bf16x4(g.act + (size_t)r * I + n, y);
+  }
+}
+
 // ------------------------------------------------- K drafts in K / k' passes
 // Before the head: the k' placeholder rows of a pass's output (rows
 // r - k' .. r - 1 of each sequence) rounded to bf16 as the LM head's input
@@ -383,6 +473,27 @@ hipError_t launch_partial_rb(const LinearArgs& a, int passes, hipStream_t st) {
   hipLaunchKernelGGL((linear_partial<RB, Q8>), dim3((a.N + a.cols - 1) / a.cols, a.ksplit, passes),
                      dim3(LinearCfg<RB, Q8>::NW * 64), 0, st, a);
   return hipGetLastError();
+}
+
+template <int RB, bool Q8>
+hipError_t launch_swiglu_rb(const LinearArgs& a, const SwigluArgs& g, int passes, hipStream_t st) {
+  hipLaunchKernelGGL((linear_swiglu<RB, Q8>), dim3((g.I / 16 + g.units - 1) / g.units, 1, passes),
+                     dim3(LinearCfg<RB, Q8>::NW * 64), 0, st, a, g);
+  return hipGetLastError();
+}
+
+template <bool Q8>
+hipError_t launch_swiglu(const LinearArgs& a, const SwigluArgs& g, int rb, int passes, hipStream_t st) {
+  switch (rb) {
+    case 1: return launch_swiglu_rb<1, Q8>(a, g, passes, st);
+    case 2: return launch_swiglu_rb<2, Q8>(a, g, passes, st);
+    case 3: return launch_swiglu_rb<3, Q8>(a, g, passes, st);
+    case 4: return launch_swiglu_rb<4, Q8>(a, g, passes, st);
+    case 5: return launch_swiglu_rb<5, Q8>(a, g, passes, st);
+    case 6: return launch_swiglu_rb<6, Q8>(a, g, passes, st);
+    case 7: return launch_swiglu_rb<7, Q8>(a, g, passes, st);
+    default: return launch_swiglu_rb<8, Q8>(a, g, passes, st);
+  }
 }
 
 template <bool Q8>
@@ -434,6 +545,7 @@ LinearPlan plan_linear(int R, int K, int N, int cus) {
       p.ksplit = (int)ks;
     }
   }
+  p.load = best;
   p.part_bytes = (size_t)p.ksplit * R * N * sizeof(float);
   return p;
 }
@@ -464,6 +576,25 @@ SemiArPlan plan_semi_ar(int B, int r, int d, int Hq, int Hkv, int I, int Lmax, i
   p.o = plan_linear(R, Hq * D, d, cus);
   p.gu = plan_linear(R, d, 2 * I, cus);
   p.down = plan_linear(R, I, d, cus);
+  // The gate / up projection in one split with SwiGLU as its epilogue, when
+  // the most loaded compute unit then streams at most 8% more than in the
+  // plan above (plan_linear's load; units of 16 gate and 16 up rows).  Fused
+  // against unfused: one sequence of 6 rows with its head (d = 4096, I =
+  // 11008) 166.4 against 170.2 us, a layer of 4 sequences at d = 8192, I =
+  // 28672 391 against 403 us (bf16) and 266.1 against 267.9 (int8).  Where
+  // the load would grow by a third (16 sequences, d = 4096, I = 14336) it
+  // gains nothing: 182.8 against 182.9 us.
+  const long long ncu = std::max(cus, 1);
+  long long best = -1;
+  for (int u = kLinearMaxUnits; u >= 1; --u) {
+    const long long g = (long long)((I / 16 + u - 1) / u) * p.gu.passes;
+    const long long load = (g + ncu - 1) / ncu * (d / kStreamChunk) * (2 * u * kLinearCols + p.gu.row_blocks * 16);
+    if (best < 0 || load < best) {
+      best = load;
+      p.gu_units = u;
+    }
+  }
+  if (best * 100 > p.gu.load * 108) p.gu_units = 0;
   p.verify = plan_verify(B, r, Hq, Hkv, D, Lmax, 1, cus);
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t o = off; off += align256(bytes); return o; };
@@ -540,9 +671,17 @@ hipError_t launch_semi_ar(const SemiArArgs& a, const SemiArPlan& p, hipStream_t 
   hipLaunchKernelGGL(epi_add_cols, eg, dim3(kEpiThreads), 0, st, part, p.o.ksplit, R, d,
                      (const float*)nullptr, x0, x1, a.ln2, h, ss);
   // act = SwiGLU(h), out = x1 + act Wdown^T
-  if ((e = lin(h, a.wgu, a.wgu_s, d, 2 * a.I, p.gu)) != hipSuccess) return e;
-  hipLaunchKernelGGL(epi_swiglu, dim3((a.I / 4 + kEpiThreads - 1) / kEpiThreads, R), dim3(kEpiThreads), 0, st, part,
-                     p.gu.ksplit, R, a.I, act, ss, (int)eg.x, d, a.eps);
+  if (p.gu_units > 0) {
+    LinearArgs la{h, a.wgu, nullptr, R, d, 2 * a.I, 1, a.wgu_s};
+    const SwigluArgs sg{act, ss, (int)eg.x, d, a.I, p.gu_units, a.eps};
+    e = a.wgu_s != nullptr ? launch_swiglu<true>(la, sg, p.gu.row_blocks, p.gu.passes, st)
+                           : launch_swiglu<false>(la, sg, p.gu.row_blocks, p.gu.passes, st);
+    if (e != hipSuccess) return e;
+  } else {
+    if ((e = lin(h, a.wgu, a.wgu_s, d, 2 * a.I, p.gu)) != hipSuccess) return e;
+    hipLaunchKernelGGL(epi_swiglu, dim3((a.I / 4 + kEpiThreads - 1) / kEpiThreads, R), dim3(kEpiThreads), 0, st, part,
+                       p.gu.ksplit, R, a.I, act, ss, (int)eg.x, d, a.eps);
+  }
   if ((e = lin(act, a.wdown, a.wdown_s, a.I, d, p.down)) != hipSuccess) return e;
   return launch_epi_add(part, p.down.ksplit, R, d, nullptr, x1, a.out, st);
 }

@@ -150,6 +150,7 @@ struct LinearPlan {
   int passes;      // passes over the weight (ceil(R / 128))
   int cols;        // output columns per work-group: 16 per wave that owns columns
   int ksplit;      // splits of the reduction
+  long long load;  // relative time of the most loaded compute unit
   size_t part_bytes;
 };
 
@@ -187,6 +188,7 @@ struct SemiArArgs {
 
 struct SemiArPlan {
   LinearPlan fc, qkv, o, gu, down;
+  int gu_units;    // > 0: gate / up with SwiGLU in one launch, this many 16-pair units per work-group
   VerifyPlan verify;
   size_t off_part, off_x0, off_h, off_q, off_attn16, off_x1, off_act, off_kvlen, off_ss, off_verify;
   size_t workspace_bytes;

@@ -253,7 +253,8 @@ __global__ __launch_bounds__(512) void lm_logits_stream(LmHeadArgs a, int base, 
   for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) acc[cb][rb] = floatx4{0.f, 0.f, 0.f, 0.f};
-  stream_product<RB, CB, NW, false>(static_cast<const uint16_t*>(a.weight) + (size_t)v0 * a.d, a.V - v0, active,
+  const int valid[CB] = {a.V - v0, a.V - v0 - 16};
+  stream_product<RB, CB, NW, false>(static_cast<const uint16_t*>(a.weight) + (size_t)v0 * a.d, (size_t)32 * a.d, valid, active,
                                     static_cast<const uint16_t*>(a.hidden), a.R, a.d, 0, nch,
                                     (int)((unsigned)(wg >> 3) % (unsigned)nch), ring, acc);
   // scaled logits to probs; the statistics of this work-group's blocks,

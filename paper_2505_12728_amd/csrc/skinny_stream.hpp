@@ -48,8 +48,9 @@ __device__ __forceinline__ void stream_for(F&& f) {
 // input, the others multiply.  Accumulator element i of lane (c, G) is row
 // 16 cb + 4 G + i of the wave's weight rows, input row 16 rb + c of the pass.
 //
-//   w0      the wave's first weight row (wave-uniform); `valid` rows of it
-//           exist, the others read as zero
+//   w0      the wave's first weight row (wave-uniform); block cb starts
+//           cb * block_bytes further on and has valid[cb] rows, the others
+//           read as zero
 //   active  false (wave-uniform): a wave without weight rows, which only
 //           meets the barriers
 //   x       first input row of the pass; `rows` of them exist, the other
@@ -99,7 +100,8 @@ __device__ __forceinline__ void stream_for(F&& f) {
 // 39.0 -> 33.0 us; 36 rows, 57344 x 8192 bf16 185.6 -> 168.7 us (5.6 TB/s),
 // int8 127.9 -> 106.6 us; 6 rows, 28672 x 4096 45.0 -> 40.8 us (5.75 TB/s).
 template <int RB, int CB, int NW, bool Q8>
-__device__ __forceinline__ void stream_product(const void* w0, int valid, bool active, const uint16_t* x, int rows,
+__device__ __forceinline__ void stream_product(const void* w0, size_t block_bytes, const int (&valid)[CB],
+                                               bool active, const uint16_t* x, int rows,
                                                int K, int ch0, int ch1, int rot, unsigned char* ring,
                                                floatx4 (&acc)[CB][RB]) {
   constexpr int COPIES = RB * 4;                // 1 KB copies per step
@@ -166,17 +168,19 @@ __device__ __forceinline__ void stream_product(const void* w0, int valid, bool a
   }
 
   const uint32_t row_bytes = (uint32_t)K * (Q8 ? 1u : 2u);
-  const auto wrsrc = stream_rsrc(w0, (uint32_t)min(max(valid, 0), 16 * CB) * row_bytes);
-  uint32_t woff[CB];
+  decltype(stream_rsrc(w0, 0u)) wrsrc[CB];
 #pragma unroll
-  for (int cb = 0; cb < CB; ++cb) woff[cb] = (uint32_t)(cb * 16 + c) * row_bytes + (uint32_t)G * (Q8 ? 16u : 32u);
+  for (int cb = 0; cb < CB; ++cb)
+    wrsrc[cb] = stream_rsrc(static_cast<const unsigned char*>(w0) + cb * block_bytes,
+                            (uint32_t)min(max(valid[cb], 0), 16) * row_bytes);
+  const uint32_t woff = (uint32_t)c * row_bytes + (uint32_t)G * (Q8 ? 16u : 32u);
   u32x4 wf[2][CB][8];
   // piece i of block cb of the group of steps t .. t + GS - 1
   auto wpiece = [&](u32x4 (&f)[CB][8], int t, int cb, int i) {
     const int ts = t + i / WS;
     const uint32_t off = ts < t1 ? (uint32_t)at(ts) * (Q8 ? 128u : 256u) : PAST;
     const uint32_t in_step = Q8 ? 64u * (i & 1) : 128u * ((i & 3) >> 1) + 16u * (i & 1);
-    f[cb][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, (int)(woff[cb] + off + in_step), 0, 0));
+    f[cb][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wrsrc[cb], (int)(woff + off + in_step), 0, 0));
   };
   auto wload = [&](u32x4 (&f)[CB][8], int t) {  // a whole group, block by block
 #pragma unroll
