@@ -8,17 +8,18 @@
 // for the r new rows of each sequence, over the draft's KV cache.
 //
 // A drafting step has few rows (R = B r <= 128 per pass), so every
-// projection streams its weight once and is bound by HBM.  One kernel
-// serves all five, around the weight stream of skinny_stream.hpp: a
-// work-group of eight waves, of which up to seven own 32 output columns each
-// over a range of 256-channel chunks of the reduction and one copies the
-// input rows.  A compute unit streams weights at a bounded rate, so the
-// planner sizes the column groups and reduction splits to give every unit
-// the same load; each split writes fp32 partial
-// sums, and one epilogue launch per projection adds the splits and applies
-// what follows it: bias + norm weight, RoPE + cache append, residual + norm
-// weight, SwiGLU, or the final residual (an RMSNorm's row factor commutes
-// with the projection after it, so that projection's epilogue applies it).  The attention is the
+// projection streams its weight once and is bound by HBM.  All five are
+// built around the weight stream of skinny_stream.hpp: a work-group of eight
+// waves, of which up to seven own 32 output columns each over a range of
+// 256-channel chunks of the reduction and one copies the input rows.  A
+// compute unit streams weights at a bounded rate, so the planner sizes the
+// column groups and reduction splits to give every unit the same load; each
+// split writes fp32 partial sums, and one epilogue launch per projection
+// adds the splits and applies what follows it: bias + norm weight, RoPE +
+// cache append, residual + norm weight, SwiGLU (in the gate / up projection
+// itself where it needs no split), or the final residual (an RMSNorm's row
+// factor commutes with the projection after it, so it is applied to that
+// projection's result).  The attention is the
 // verification kernel (writing the bf16 input of Wo itself): the new
 // rows are a block of r queries, causal inside the block, over the cache.
 #include <math.h>

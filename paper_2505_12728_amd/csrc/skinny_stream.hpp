@@ -67,11 +67,11 @@ __device__ __forceinline__ void stream_for(F&& f) {
 // multiplied, its loads back to back at the group's start, one 16-row block
 // after the other, so that a row's 512 bytes reach HBM together (issued piece
 // by piece over both blocks, bf16 is up to 24% slower: 6 rows, 8192 x 28672
-// 82 -> 102 us).  Int8 rows of 16 or of more
-// than 64 input rows are refilled piece by piece: their products take so
-// long that the burst would come late (6 rows, 8192 x 28672 53 -> 47 us; 112
-// rows, 57344 x 8192 142 -> 128 us).  The lanes' share of a group is such that both types sum the
-// same products in the same order, and that a load touches one 128-byte
+// 82 -> 102 us).  Int8 weights under at most 16 or under 65 to 112 input rows
+// are refilled piece by piece: their products take so long that the burst
+// would come late (6 rows, 8192 x 28672 53 -> 47 us; 112 rows, 57344 x 8192
+// 142 -> 128 us).  The lanes' share of a group is such that both types sum
+// the same products in the same order, and that a load touches one 128-byte
 // line per row.
 //
 // The input rows of a step are copied L2 -> LDS by the buffer_load ... lds
