@@ -179,7 +179,12 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
 // 1 / sqrt(mean(y^2) + eps), one per row, commutes with the projection, whose
 // epilogue applies it (row_scale); a launch of its own for it took 3.8 us (6
 // rows) to 4.8 us (112 rows) in the layer, twice.
+// The factor is 0 where the mean square overflows.  A value whose square
+// overflows enters h as 0 y, as the factor would make it: 0 if it is finite,
+// so that no product of the row overflows (and 0 times it stays 0), NaN if it
+// is infinite, so that every normalised value of its row is NaN.
 constexpr int kEpiCols = 4 * kEpiThreads;
+__device__ __forceinline__ float norm_input(float y) { return y * y == INFINITY ? 0.f * y : y; }
 __global__ __launch_bounds__(kEpiThreads) void epi_add_cols(const float* part, int ksplit, int R, int N,
                                                             const float* bias, const float* residual,
                                                             float* out, const float* norm_w, __bf16* h,
@@ -208,7 +213,7 @@ __global__ __launch_bounds__(kEpiThreads) void epi_add_cols(const float* part, i
       if (h != nullptr) {
         Pack8 pk;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) pk.b[j] = float_to_bf16(y[j] * norm_w[n0 + j]);
+        for (int j = 0; j < 4; ++j) pk.b[j] = float_to_bf16(norm_input(y[j]) * norm_w[n0 + j]);
         *reinterpret_cast<u32x2*>(h + row + n0) = u32x2{pk.u[0], pk.u[1]};
       }
       s2 = y[0] * y[0] + y[1] * y[1] + y[2] * y[2] + y[3] * y[3];
@@ -222,7 +227,7 @@ __global__ __launch_bounds__(kEpiThreads) void epi_add_cols(const float* part, i
       if (bias) y += bias[n];
       if (residual) y += residual[row + n];
       out[row + n] = y;
-      if (h != nullptr) h[row + n] = float_to_bf16(y * norm_w[n]);
+      if (h != nullptr) h[row + n] = float_to_bf16(norm_input(y) * norm_w[n]);
       s2 += y * y;
     }
   }
@@ -244,13 +249,6 @@ __device__ __forceinline__ float row_scale(const float* ss, int nblk, int r, int
   }
   return 1.f / sqrtf(t / (float)d + eps);
 }
-// A row whose mean square overflows has scale 0: its normalised values are 0
-// even where the unscaled projection overflowed.
-__device__ __forceinline__ float scaled(float x, float inv) { return inv == 0.f ? 0.f : x * inv; }
-__device__ __forceinline__ floatx4 scaled(const floatx4& x, float inv) {
-  return floatx4{scaled(x[0], inv), scaled(x[1], inv), scaled(x[2], inv), scaled(x[3], inv)};
-}
-
 static int epi_blocks(int N) { return (N + kEpiCols - 1) / kEpiCols; }
 
 // Fused projection output of row r (sequence b = r / rows, j = r % rows,
@@ -296,7 +294,7 @@ __global__ __launch_bounds__(kEpiThreads) void epi_rope_qkv(const float* part, i
     const size_t idx[2] = {base, base + half};
     floatx4 x[2];
     split_sum4(part, ksplit, stride, idx, x);
-    const floatx4 x0 = scaled(x[0], inv), x1 = scaled(x[1], inv);
+    const floatx4 x0 = x[0] * inv, x1 = x[1] * inv;
     floatx4 y0, y1;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -318,7 +316,7 @@ __global__ __launch_bounds__(kEpiThreads) void epi_rope_qkv(const float* part, i
     const size_t idx[1] = {(size_t)r * N + (size_t)(Hq + Hkv) * D + e4};
     floatx4 v[1];
     split_sum4(part, ksplit, stride, idx, v);
-    store_bf16x4(vc + ((size_t)b * Lmax + p) * Hkv * D + e4, scaled(v[0], inv));
+    store_bf16x4(vc + ((size_t)b * Lmax + p) * Hkv * D + e4, v[0] * inv);
   }
 }
 
@@ -336,7 +334,7 @@ __global__ __launch_bounds__(kEpiThreads) void epi_swiglu(const float* part, int
   const float inv = row_scale(ss, nblk, r, d, eps);
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    const float g = scaled(x[0][e], inv), u = scaled(x[1][e], inv);
+    const float g = x[0][e] * inv, u = x[1][e] * inv;
     y[e] = g / (1.f + expf(-g)) * u;
   }
   store_bf16x4(act + (size_t)r * I + i, y);
@@ -419,7 +417,7 @@ __global__ __launch_bounds__((LinearCfg<RB, Q8>::NW * 64)) void linear_swiglu(Li
     floatx4 y;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const float gv = scaled(acc[0][rb][e], inv), u = scaled(uv[rb][e], inv);
+      const float gv = acc[0][rb][e] * inv, u = uv[rb][e] * inv;
       y[e] = gv / (1.f + expf(-gv)) * u;
     }
     store_bf16x4(g.act + (size_t)r * I + n, y);
