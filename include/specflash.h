@@ -444,8 +444,8 @@ int sd_linear(const void* x, const void* w, const float* bias, const float* resi
  *   workspace  sd_semi_ar_layer_workspace_size(...) bytes, 256-byte aligned
  *            (device-dependent like sd_linear's)
  * Requirements: d = Hq * D with D in {64, 128}; Hq % Hkv == 0; 1 <= r <= 16;
- * r * (Hq / Hkv) <= 256; d and I multiples of 256; Lmax >= r; B * r <=
- * 65535; eps >= 0; theta > 0.  Errors as for sd_linear.
+ * r * (Hq / Hkv) <= 256; d and I multiples of 256, 2d and I below 2^26;
+ * Lmax >= r; B * r <= 65535; eps >= 0; theta > 0.  Errors as for sd_linear.
  * ---------------------------------------------------------------------- */
 size_t sd_semi_ar_layer_workspace_size(int B, int r, int d, int num_q_heads, int num_kv_heads,
                                        int I, int Lmax);

@@ -67,7 +67,7 @@ __global__ __launch_bounds__((LinearCfg<RB, Q8>::NW * 64)) void linear_partial(L
   const int r0 = blockIdx.z * RB * 16;
   const int K = a.K, N = a.N, R = a.R;
   const int nch = K / kStreamChunk;
-  const int ch0 = (int)((unsigned)nch * (unsigned)ks / (unsigned)a.ksplit);   // nch <= 2^12, ksplit <= 16
+  const int ch0 = (int)((unsigned)nch * (unsigned)ks / (unsigned)a.ksplit);   // nch < 2^18, ksplit <= 16
   const int ch1 = (int)((unsigned)nch * (unsigned)(ks + 1) / (unsigned)a.ksplit);
   // Work-groups in step would read the same channels of every row, rows a
   // multiple of a kilobyte apart, which keeps few channels of their XCD's L2
@@ -513,9 +513,10 @@ hipError_t launch_partial(const LinearArgs& a, int rb, int passes, hipStream_t s
 
 LinearPlan plan_linear(int R, int K, int N, int cus) {
   LinearPlan p{};
-  const int rows = std::min(R, kLinearRowsPerPass);
+  const int pass_rows = 16 * std::max(1, stream_row_blocks(K));   // the caller refuses a K without a row block
+  const int rows = std::min(R, pass_rows);
   p.row_blocks = (rows + 15) / 16;
-  p.passes = (R + kLinearRowsPerPass - 1) / kLinearRowsPerPass;
+  p.passes = (R + pass_rows - 1) / pass_rows;
   constexpr int wide = kLinearCols;
   // one work-group per compute unit: its registers hold no second one
   const long long cap = std::max(cus, 1);

@@ -133,6 +133,14 @@ hipError_t launch_philox_uniforms(uint64_t seed, uint64_t offset, float* u, int 
 
 // ------------------------------------------------- draft semi-AR layer
 constexpr int kLinearRowsPerPass = 128;   // input rows per pass of the weight stream
+// 16-row blocks (0 .. 8) of input rows of K channels that one pass of the
+// weight stream may take: its buffer ranges and offsets are 32-bit, the upper
+// half of which means "past the range", so that the rows of a pass, and 16
+// weight rows, have to end below 2^31 bytes.
+inline int stream_row_blocks(long long K) {
+  const long long blocks = ((1LL << 31) - 1) / (16 * 2 * K);
+  return (int)(blocks < kLinearRowsPerPass / 16 ? blocks : kLinearRowsPerPass / 16);
+}
 constexpr int kLinearMaxSplits = 16;      // reduction splits at most
 
 struct LinearArgs {
@@ -147,7 +155,7 @@ struct LinearArgs {
 
 struct LinearPlan {
   int row_blocks;  // 16-row blocks per pass (1..8)
-  int passes;      // passes over the weight (ceil(R / 128))
+  int passes;      // passes over the weight (ceil(R / 128) up to 2^22 channels)
   int cols;        // output columns per work-group: 16 per wave that owns columns
   int ksplit;      // splits of the reduction
   long long load;  // relative time of the most loaded compute unit

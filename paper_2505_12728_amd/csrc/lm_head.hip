@@ -370,7 +370,7 @@ __global__ __launch_bounds__(256) void lm_normalize(LmHeadArgs a, int npairs) {
 template <int RB>
 hipError_t launch_rb(const LmHeadArgs& a, hipStream_t st, int* npairs) {
   if constexpr (RB <= 8) {
-    if (a.d % kStreamChunk == 0) {
+    if (a.d % kStreamChunk == 0 && RB <= stream_row_blocks(a.d)) {
       // rounds of up to seven units per work-group, one work-group per
       // compute unit (its registers hold no second one; two smaller ones, of
       // one 16-row block per wave, measured the same to 6% slower)

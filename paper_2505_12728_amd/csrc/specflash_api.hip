@@ -491,6 +491,8 @@ static bool semi_ar_shape_ok(int B, int r, int d, int Hq, int Hkv, int I, int Lm
   if (r > 16 || (D != 64 && D != 128) || r * (Hq / Hkv) > 256 || d % 256 != 0 || I % 256 != 0 ||
       Lmax < r || (long long)B * r > 65535 || (long long)B * Lmax * Hkv * D > (1LL << 40))
     return false;
+  // every projection's reduction (2d, d and I channels) fits the weight stream
+  if (sd::stream_row_blocks(2LL * d) < 1 || sd::stream_row_blocks(I) < 1) return false;
   *status = SD_OK;
   return true;
 }

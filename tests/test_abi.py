@@ -319,6 +319,10 @@ def test_semi_ar_layer_validation_errors(lib):
     assert call(wsb=64) == sd.SD_ERR_WORKSPACE
     assert lib.sd_semi_ar_layer_workspace_size(2, 9, 1024, 8, 2, 2048, 64) > 2 * 9 * 2048 * 2
     assert lib.sd_semi_ar_layer_workspace_size(2, 17, 1024, 8, 2, 2048, 64) == 0
+    # widths whose 16 rows reach 2^31 bytes are refused, narrower ones are not
+    assert lib.sd_semi_ar_layer_workspace_size(1, 1, 256, 4, 4, 1 << 26, 64) == 0
+    assert lib.sd_semi_ar_layer_workspace_size(1, 1, 256, 4, 4, (1 << 26) - 256, 64) > 0
+    assert lib.sd_semi_ar_layer_workspace_size(1, 1, 1 << 25, 1 << 18, 1, 256, 64) == 0
 
 
 def test_semi_ar_draft_validation_errors(lib):
