@@ -74,6 +74,30 @@ def test_compress_q8_edge_cases(case):
     assert_close(out, oracle_full(q, H, scale), "bf16", name)
 
 
+# Enough (sequence, head) pairs that the tokens are not split: 8 to 14 tiles
+# per work-group, so that the steady loop of the rings for up to four waves
+# runs once or twice and is left at each of its six phases, with a last tile
+# of one token (and once a full one); one, two and four waves; peaked and
+# diffuse scores.  One head of every sequence is compared.
+@pytest.mark.parametrize("C", [20, 64, 128])
+@pytest.mark.parametrize("N", [449, 513, 577, 641, 705, 769, 833, 896])
+def test_compress_q8_steady_loop(C, N):
+    B, H = 32, 8
+    scale = 1.0 if N // 64 % 2 else 1 / math.sqrt(128)
+    w = synth.Workload("steady", "bf16", batch=1, hq=1, hkv=1, head_dim=64, kv_len=1, block=1,
+                       c_batch=B, c_tokens=N, c_width=H * 128, c_latents=C, c_heads=H)
+    q = synth.compress_q8_inputs(w, seed=N + C)
+    out = run_gpu(q, H, scale)
+    assert np.all(np.isfinite(out))
+    got, ref = [], []
+    for b in range(B):
+        cols = slice((b % H) * 128, (b % H + 1) * 128)
+        got.append(out[b, :, cols])
+        ref.append(oracle.latent_compress_q8(q["latents_q"][:, cols], q["latent_exp"], q["feats_q"][b:b + 1, :, cols],
+                                             q["feat_exp"][b:b + 1], 1, scale)[0])
+    assert_close(np.stack(got), np.stack(ref), "bf16", f"N{N} C{C}")
+
+
 def test_compress_q8_exponent_range_ends_and_zero_rows():
     # exponents at both ends of [-14, 9] on a mix of tokens, all-zero rows,
     # latents at the ends too; every value is exact in fp16

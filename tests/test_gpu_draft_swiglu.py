@@ -2,7 +2,8 @@
 its tiles: rows around the 16-row blocks, the 64 rows where an int8
 work-group changes its waves, and the 128-row pass; intermediate widths whose
 16-pair units fill the last work-group, leave it ragged, or are fewer than
-the compute units; one shape whose reduction is split instead.
+the compute units; 3 and 5 chunks of the reduction, at each of which some
+work-group starts; one shape whose reduction is split instead.
 
 Reference: the oracle, with the bounds of tests/test_gpu_draft.py.  Int8
 weights with power-of-two scales are exact in bf16 and both types sum in the
@@ -23,7 +24,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("B,r,hq,hkv,D,I", [
     (1, 1, 4, 4, 64, 256), (1, 16, 4, 2, 64, 11008), (17, 1, 4, 4, 64, 768), (6, 8, 2, 1, 128, 4352),
     (8, 8, 4, 4, 64, 11008), (5, 13, 4, 1, 64, 4352), (10, 11, 4, 2, 64, 8448), (8, 16, 4, 4, 64, 512),
-    (43, 3, 4, 4, 64, 4352), (3, 2, 16, 4, 128, 256)])
+    (43, 3, 4, 4, 64, 4352), (3, 2, 16, 4, 128, 256),
+    (2, 5, 12, 4, 64, 11008), (9, 9, 20, 4, 64, 4352), (6, 16, 10, 2, 128, 8448)])
 def test_fused_swiglu_edges(B, r, hq, hkv, D, I):
     import torch
     import paper_2505_12728_amd as sd

@@ -61,18 +61,21 @@ def test_lm_head_long_video_every_row():
 @pytest.mark.parametrize("R,d,V,tau", [(1, 64, 1, 1.0), (1, 64, 37, 0.5), (5, 128, 1000, 0.05),
                                        (17, 192, 300, 20.0), (65, 64, 129, 1.0),
                                        (130, 128, 2050, 0.7),
-                                       # widths d % 256 == 0 with R <= 64 (the
-                                       # 512-byte-run kernel): one entry, a
-                                       # partial tile, an odd chunk count, the
-                                       # largest row count, 8-wave tiles with a
-                                       # ragged end and unaligned rows
+                                       # widths d % 256 == 0 with R <= 128 (the
+                                       # weight stream): one entry, partial
+                                       # units, odd chunk counts, one to eight
+                                       # 16-row blocks, one and two rounds of
+                                       # work-groups with starts at every
+                                       # chunk, ragged ends and unaligned rows
                                        (1, 256, 1, 1.0), (3, 256, 50, 0.5),
                                        (16, 512, 1000, 1.0), (33, 768, 129, 2.0),
-                                       (64, 256, 65600, 0.7), (49, 1024, 70001, 0.3)])
+                                       (64, 256, 65600, 0.7), (49, 1024, 70001, 0.3),
+                                       (65, 768, 9001, 1.0), (80, 1280, 70001, 0.7),
+                                       (90, 1280, 9001, 0.5), (112, 512, 20017, 1.0),
+                                       (128, 768, 20017, 0.7)])
 def test_lm_head_edge_shapes(R, d, V, tau):
-    # ragged rows (row blocks of 16, launches of 64), ragged vocabulary
-    # (tiles of 64 / 128, blocks of 16), odd channel groups, extreme
-    # temperatures
+    # ragged rows (row blocks of 16), ragged vocabulary (units of 32 or tiles
+    # of 64 / 128, blocks of 16), odd channel groups, extreme temperatures
     w = synth.workload("llava-7b-image")
     rs = synth.streams(1234 + R + V)
     hidden = synth.Tensor(rs["lm_hidden"].normal((R, d)), "bf16")
