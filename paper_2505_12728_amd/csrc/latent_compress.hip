@@ -97,7 +97,8 @@ __device__ __forceinline__ void map_tile(int lin, int n_bh, int n_lt, int& bh, i
 
 // One work-group = NW waves x 32 latents of one (sequence, head), one token
 // split.  64-token tiles of F_V[b][:, hs] are copied HBM -> LDS by the
-// global_load_lds DMA into a ring of four buffers.  One tile ahead of its
+// global_load_lds DMA into a ring of four buffers (bf16 input; int8 input: a
+// staging ring beside the fp16 one, see CompressLds).  One tile ahead of its
 // score step, the work-group converts a tile from bf16 to fp16 (each
 // 16-byte piece once per work-group), so every wave then runs the P V
 // product on fp16 matrix cores with no per-wave conversion:
@@ -119,7 +120,7 @@ __device__ __forceinline__ void map_tile(int lin, int n_bh, int n_lt, int& bh, i
 // last group, so the next step's first reads overlap that group's work).
 template <int NW, int DH, bool IN8>
 constexpr bool kChannelMajor = !IN8 && NW == 8 && DH == 128;
-template <int NW, int DH, bool IN8>
+template <int NW, int DH, bool IN8, bool PAIR>
 struct CompressLds {
   static constexpr bool CM = kChannelMajor<NW, DH, IN8>;
   unsigned char ring[4][64 * DH * 2];                       // bf16 tiles (CM) / fp16 tiles
@@ -127,29 +128,26 @@ struct CompressLds {
   unsigned char stage[IN8 ? 4 : 1][IN8 ? 64 * DH : 16];    // int8 staging tiles
   int8_t sexp[IN8 ? kQ8MaxSplit : 4];                      // int8: the split's token exponents
 };
-// int8 input, up to four waves: the fp16 ring holds the tile of P V, that of the scores and
-// the one being converted, the staging ring the tile being converted and
-// the one in flight, so three and two slots are enough: 80 KB with the
-// exponents, two work-groups per compute unit where four slots of each held
-// one (16 sequences of 1024 tokens, 128 latents, 32 heads: 61.9 -> 48.1 us; 7
-// of 3001, 70 latents, 64 heads: 128.6 -> 100.0 us).
-template <int DH>
-struct CompressLdsQ8Small {
+// PAIR (int8 input, up to four waves): the fp16 ring holds the tile of P V,
+// that of the scores and the one being converted, the staging ring the tile
+// being converted and the one in flight, so three and two slots are enough:
+// 80 KB with the exponents, two work-groups per compute unit where four slots
+// of each hold one (CompressPlan::pair has the measurements).
+template <int NW, int DH>
+struct CompressLds<NW, DH, true, true> {
+  static_assert(NW <= 4, "two work-groups of up to four waves");
   unsigned char ring[3][64 * DH * 2];                       // fp16 tiles
   unsigned char stage[2][64 * DH];                          // int8 staging tiles
   int8_t sexp[kQ8MaxSplit];                                 // the split's token exponents
 };
-template <int DH> struct CompressLds<1, DH, true> : CompressLdsQ8Small<DH> {};
-template <int DH> struct CompressLds<2, DH, true> : CompressLdsQ8Small<DH> {};
-template <int DH> struct CompressLds<4, DH, true> : CompressLdsQ8Small<DH> {};
 
 // The matrix-core pass of a work-group (NW waves x 32 latents of one
 // (sequence, head), one token split).  Returns, per thread, the range flags
 // of its outputs (bf16 input): bit 0 set when an accumulator is not finite,
 // bit 1 set when some output it wrote has magnitude 2^-12 or more.
-template <int NW, int DH, bool IN8>
+template <int NW, int DH, bool IN8, bool PAIR>
 __device__ __forceinline__ unsigned compress_pass(const CompressArgs a, int n_bh, int n_lt, int tokens_per_split,
-                                                  int nsplit, CompressLds<NW, DH, IN8>& sm) {
+                                                  int nsplit, CompressLds<NW, DH, IN8, PAIR>& sm) {
   constexpr int TT = 64;                    // tokens per tile
   constexpr int DC = DH / 32;               // 32-channel slices (QK)
   constexpr int DB = DH / 16;               // 16-channel output blocks (PV)
@@ -162,10 +160,9 @@ __device__ __forceinline__ unsigned compress_pass(const CompressArgs a, int n_bh
   constexpr int DMA = IN_PIECES / 64;       // 64-lane copies per tile
   constexpr int DMA_PER_WAVE = DMA / NW;
   constexpr int CVT_PER_THREAD = IN_PIECES / (NW * 64);   // input pieces converted per thread
-  constexpr bool SMALL8 = IN8 && NW <= 4;
-  constexpr int NBUF = SMALL8 ? 3 : 4;      // ring slots
-  constexpr int NIN = SMALL8 ? 2 : 4;       // slots of the copies' ring (bf16: the ring itself)
-  constexpr int UNROLL = SMALL8 ? 6 : 4;    // steps after which both repeat
+  constexpr int NBUF = PAIR ? 3 : 4;        // ring slots
+  constexpr int NIN = PAIR ? 2 : 4;         // slots of the copies' ring (bf16: the ring itself)
+  constexpr int UNROLL = PAIR ? 6 : 4;      // steps after which both repeat
   constexpr float kRescale = 15.f;      // P = exp2(s - m) <= 2^15 < the fp16 maximum
   static_assert(DMA % NW == 0 && IN_PIECES % (NW * 64) == 0, "tile work must split evenly");
   static_assert(!IN8 || DH == 128, "int8 input: 128-channel heads");
@@ -525,7 +522,8 @@ __device__ __forceinline__ unsigned compress_pass(const CompressArgs a, int n_bh
     __builtin_amdgcn_sched_group_barrier(0x002, (N), ID);                                  \
   }
 
-  // Ring schedule (4 buffers), software-pipelined across tiles.  Entering
+  // Ring schedule (NBUF slots of fp16 tiles, NIN of the copies; one ring for
+  // bf16 input), software-pipelined across tiles.  Entering
   // step it, scur holds the scores of tile it and the running maxima already
   // cover them.  After one barrier the step runs NG groups; each waits for
   // its own LDS reads (issued one group earlier), issues the next group's
@@ -550,7 +548,7 @@ __device__ __forceinline__ unsigned compress_pass(const CompressArgs a, int n_bh
   constexpr int KPG = 4 / NQK;         // 16-token blocks per QK group
   issue(0, 0);
   issue(min(1, last), 1);
-  if constexpr (SMALL8) {
+  if constexpr (PAIR) {
     wait_vm_then_barrier<DMA_PER_WAVE>();             // tile 0 landed
     convert(0, 0);
     wait_vm_then_barrier<0>();                        // tile 1 landed, tile 0 converted
@@ -669,12 +667,13 @@ __device__ __forceinline__ unsigned compress_pass(const CompressArgs a, int n_bh
   u32x4 xr[2][4];
 
   // one step; the mask flag (compile time) is set only for it = last - 1, so
-  // the steady-state loop has no branch between its groups.  The ring phase
-  // PH = it % NBUF is a compile-time constant in the unrolled main loop (the
+  // the steady-state loop has no branch between its groups.  The rings' phase
+  // PH = it % UNROLL is a compile-time constant in the unrolled main loop (the
   // slots' offsets then sit in the LDS instructions' offset fields) and -1
-  // elsewhere (offsets added at run time).  Entering a step: tile it+1
-  // converted by every wave, tile it+2 landed, the copy of tile it+3 issued
-  // and (kRot) the first group's reads done.
+  // elsewhere (offsets added at run time).  Entering a step (kRot), or after
+  // the barrier and copy it begins with: tile it+1 converted by every wave,
+  // tile it+2 landed, the copy of tile it+3 issued and (kRot) the first
+  // group's reads done.
   auto step = [&](int it, auto mask_tag, auto ph_tag) {
     constexpr int PH = decltype(ph_tag)::value;
     // offset of the slot of tile it + K in a ring of NS slots of SZ bytes
@@ -980,14 +979,14 @@ __device__ __forceinline__ void compress_exact_wave(const CompressArgs& a, int b
   }
 }
 
-template <int NW, int DH, bool IN8>
+template <int NW, int DH, bool IN8, bool PAIR>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) void compress_bf16(CompressArgs a, int n_bh, int n_lt,
                                                          int tokens_per_split, int nsplit) {
-  __shared__ __align__(16) CompressLds<NW, DH, IN8> sm;
+  __shared__ __align__(16) CompressLds<NW, DH, IN8, PAIR> sm;
   if constexpr (IN8) {
-    compress_pass<NW, DH, true>(a, n_bh, n_lt, tokens_per_split, nsplit, sm);
+    compress_pass<NW, DH, true, PAIR>(a, n_bh, n_lt, tokens_per_split, nsplit, sm);
   } else {
-    const unsigned f = compress_pass<NW, DH, false>(a, n_bh, n_lt, tokens_per_split, nsplit, sm);
+    const unsigned f = compress_pass<NW, DH, false, false>(a, n_bh, n_lt, tokens_per_split, nsplit, sm);
     // the wave's verdict (no barrier): rerun its latents exactly when some
     // accumulator is not finite, or when it has latents and every output
     // is below 2^-12
@@ -1204,7 +1203,14 @@ template <int NW, int DH, bool IN8>
 hipError_t launch_bf16(const CompressArgs& a, const CompressPlan& p, hipStream_t st) {
   const int n_bh = a.B * a.H;
   dim3 grid(n_bh * p.lat_tiles, p.nsplit);
-  hipLaunchKernelGGL((compress_bf16<NW, DH, IN8>), grid, dim3(NW * 64), 0, st, a, n_bh, p.lat_tiles,
+  if constexpr (IN8 && NW <= 4) {
+    if (p.pair) {
+      hipLaunchKernelGGL((compress_bf16<NW, DH, IN8, true>), grid, dim3(NW * 64), 0, st, a, n_bh, p.lat_tiles,
+                         p.tokens_per_split, p.nsplit);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((compress_bf16<NW, DH, IN8, false>), grid, dim3(NW * 64), 0, st, a, n_bh, p.lat_tiles,
                      p.tokens_per_split, p.nsplit);
   return hipGetLastError();
 }
@@ -1261,6 +1267,15 @@ CompressPlan plan_compress(int B, int N, int C, int d, int H, int dtype, int cus
     p.tokens_per_split = (int)tps;
   }
   p.nsplit = std::max(1, (N + p.tokens_per_split - 1) / p.tokens_per_split);
+  // Two int8 work-groups of up to four waves per compute unit (CompressLds'
+  // three- and two-slot rings) once there are more than compute units: back
+  // to back, 16 sequences of 1024 tokens, 128 latents, 32 heads 58.6 -> 45.8
+  // us, 7 of 3001, 70 latents, 64 heads 128.6 -> 100.0 us.  Up to one each,
+  // they only lose: the smaller rings start with one tile less in flight (in
+  // a graph, one sequence of 8192 tokens, 100 latents, 32 heads: 35.4 us with
+  // four slots, 37.3 us with three and two; 4 of 3001, 28 heads 47.2 and 48.9;
+  // 36 of the 180 shapes of up to 128 latents tried lost 3 to 5%).
+  p.pair = dtype == kCompressInt8 && p.lat_tile <= 128 && n_bh * p.lat_tiles * p.nsplit > std::max(cus, 1);
   p.workspace_bytes = p.nsplit > 1
       ? (size_t)n_bh * p.nsplit * C * ((size_t)p.dh + 1) * sizeof(float) : 0;
   return p;

@@ -58,6 +58,7 @@ struct CompressPlan {
   int lat_tiles;
   int nsplit;          // splits of the N tokens
   int tokens_per_split;
+  bool pair;           // int8 input, up to 128 latents: two work-groups per compute unit
   size_t workspace_bytes;
 };
 

@@ -75,14 +75,16 @@ def test_compress_q8_edge_cases(case):
 
 
 # Enough (sequence, head) pairs that the tokens are not split: 8 to 14 tiles
-# per work-group, so that the steady loop of the rings for up to four waves
-# runs once or twice and is left at each of its six phases, with a last tile
-# of one token (and once a full one); one, two and four waves; peaked and
-# diffuse scores.  One head of every sequence is compared.
+# per work-group, so that the steady loop (six steps at two work-groups per
+# compute unit, four at one) runs and is left at each of its phases, with a
+# last tile of one token (and once a full one); one, two and four waves; 264
+# work-groups and 256, one per compute unit of an MI355X; peaked and diffuse
+# scores.  One head of every sequence is compared.
 @pytest.mark.parametrize("C", [20, 64, 128])
 @pytest.mark.parametrize("N", [449, 513, 577, 641, 705, 769, 833, 896])
-def test_compress_q8_steady_loop(C, N):
-    B, H = 32, 8
+@pytest.mark.parametrize("B", [32, 33])
+def test_compress_q8_steady_loop(C, N, B):
+    H = 8
     scale = 1.0 if N // 64 % 2 else 1 / math.sqrt(128)
     w = synth.Workload("steady", "bf16", batch=1, hq=1, hkv=1, head_dim=64, kv_len=1, block=1,
                        c_batch=B, c_tokens=N, c_width=H * 128, c_latents=C, c_heads=H)
@@ -95,7 +97,7 @@ def test_compress_q8_steady_loop(C, N):
         got.append(out[b, :, cols])
         ref.append(oracle.latent_compress_q8(q["latents_q"][:, cols], q["latent_exp"], q["feats_q"][b:b + 1, :, cols],
                                              q["feat_exp"][b:b + 1], 1, scale)[0])
-    assert_close(np.stack(got), np.stack(ref), "bf16", f"N{N} C{C}")
+    assert_close(np.stack(got), np.stack(ref), "bf16", f"B{B} N{N} C{C}")
 
 
 def test_compress_q8_exponent_range_ends_and_zero_rows():
