@@ -998,9 +998,10 @@ hipError_t launch_stream(const VerifyArgs& a, const VerifyPlan& p, hipStream_t s
 
 // one work-group per pair, four key groups (two where a tile has too few
 // 64-lane copies for sixteen waves)
+constexpr int direct_key_groups(int row_blocks, int D) { return row_blocks == 4 && D == 64 ? 2 : 4; }
 template <int D, int NWR, bool PAGED>
 hipError_t launch_direct(const VerifyArgs& a, const VerifyPlan& p, hipStream_t st) {
-  constexpr int KG = NWR == 4 && D == 64 ? 2 : 4;
+  constexpr int KG = direct_key_groups(NWR, D);
   const int pairs = a.B * a.Hkv * p.row_groups;
   hipLaunchKernelGGL((verify_stream_bf16<D, NWR, KG, 2 * KG + 1, PAGED, true>), dim3(pairs),
                      dim3(NWR * KG * 64), 0, st, a, pairs, p.row_groups);
@@ -1057,9 +1058,9 @@ VerifyPlan plan_verify(int B, int k, int Hq, int Hkv, int D, int capacity, int d
   } else {
     // one wave per 16-row block, 1, 2 or 4 blocks per work-group.  Blocks
     // of 4 run as 8 waves in two key groups over a 128 KB ring, one work-
-    // group per compute unit; smaller ones hold a 64 KB ring, two per unit
-    // (stream_cfg).  The grid is that many work-groups, whatever the
-    // lengths.
+    // group per compute unit; smaller ones hold a ring of 64 KB, or 80 KB for
+    // one block in two key groups, two per unit (stream_cfg).  The grid is
+    // that many work-groups, whatever the lengths.
     p.row_blocks = blocks16 <= 1 ? 1 : (blocks16 == 2 ? 2 : 4);
     p.row_groups = (blocks16 + p.row_blocks - 1) / p.row_blocks;
     p.rows_wg = p.row_blocks * 16;
@@ -1076,8 +1077,13 @@ VerifyPlan plan_verify(int B, int k, int Hq, int Hkv, int D, int capacity, int d
     // (draft layer of 16 sequences, 240 positions: 193.5 -> 186.2 us; one
     // sequence with the head, 128 positions: 181.4 -> 172.1 us).  Longer
     // caches leave too few work-groups (1024 keys, 8 pairs of 64 rows: 18.0 us
-    // split, 25.4 us so).
-    p.direct = capacity <= 8 * kTile;
+    // split, 25.4 us so).  4 to 2048 pairs of 6 to 256 rows at 32 to 256
+    // positions are all faster so (D = 128, calls in a graph: 8 pairs of 64
+    // rows 17.4 -> 7.7 us at 32 positions, 14.0 -> 12.5 at 256; 64 pairs 19.8
+    // -> 8.2 and 18.1 -> 13.5; 512 pairs 55.7 -> 16.5 and 65.5 -> 35.2).  The
+    // launch counts its threads in 32 bits; more pairs take the split stream.
+    p.direct = capacity <= 8 * kTile &&
+               pairs * p.row_blocks * direct_key_groups(p.row_blocks, D) * 64 < (1LL << 32);
     // tile indices are 32-bit on the device
     if (pairs * ((capacity + kTile - 1) / kTile) >= (1LL << 30)) p.ok = false;
     p.part_rows = (size_t)(pairs + p.stream_wgs) * p.key_groups * p.rows_wg;

@@ -55,3 +55,30 @@ def test_verify_one_row_block_few_tiles(kv, k, hq, hkv, D, B, paged):
                                      page_table=d["page_table"])
     assert_close(out, ro, "bf16", "out")
     assert_lse_close(lse, rl, "bf16", "lse")
+
+
+def test_verify_short_more_pairs_than_one_launch_holds():
+    # 2^23 pairs of 17 rows are 2^32 threads at one work-group per pair: they
+    # take the split stream.  One key per sequence, so every row is its head's
+    # value row, exactly.
+    import torch
+    import paper_2505_12728_amd as sd
+    B, hkv, g, D = 64, 1 << 17, 17, 64
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    torch.cuda.empty_cache()
+    q = torch.ones(B, 1, hkv * g, D, dtype=torch.bfloat16, device="cuda")
+    kc = torch.ones(B, 1, hkv, D, dtype=torch.bfloat16, device="cuda")
+    vc = torch.empty_like(kc)
+    for b in range(B):
+        vc[b] = torch.randn(1, hkv, D, generator=gen, device="cuda").bfloat16()
+    kv = torch.ones(B, dtype=torch.int32, device="cuda")
+    kv[5] = 0
+    out, lse = sd.sd_verify_attention(q, kc, vc, kv, scale=0.125, lse=True)
+    vc[5] = 0
+    for b in range(B):
+        assert torch.equal(out[b].view(hkv, g, D), vc[b, 0].float()[:, None].expand(hkv, g, D)), b
+    want = torch.full((B,), 64 * 0.125, device="cuda")
+    want[5] = float("-inf")
+    assert torch.allclose(lse, want[:, None, None].expand_as(lse), rtol=1e-6)
+    del q, kc, vc, out, lse
+    torch.cuda.empty_cache()                    # 127 GB with the workspace
