@@ -61,18 +61,24 @@ __device__ __forceinline__ void stream_for(F&& f) {
 //
 // The stream is bound by HBM, so everything else has to stay out of the way
 // of the weight loads.  The reduction advances in steps of 128 channels.
-// Weights go to registers in groups of eight 16-byte loads per lane and
-// 16-row block, 512 bytes of each row (two steps of bf16, four of int8).
-// Two groups of registers take turns: one is loaded while the other is
-// multiplied, its loads back to back at the group's start, one 16-row block
-// after the other, so that a row's 512 bytes reach HBM together (issued piece
-// by piece over both blocks, bf16 is up to 24% slower: 6 rows, 8192 x 28672
-// 82 -> 102 us).  Int8 weights under at most 16 or under 65 to 112 input rows
-// are refilled piece by piece: their products take so long that the burst
-// would come late (6 rows, 8192 x 28672 53 -> 47 us; 112 rows, 57344 x 8192
-// 142 -> 128 us).  The lanes' share of a group is such that both types sum
-// the same products in the same order, and that a load touches one 128-byte
-// line per row.
+// Weights go to registers in groups of two steps: eight 16-byte loads per
+// lane and 16-row block for bf16, 512 bytes of each row, four and 256 bytes
+// for int8.  Two groups of registers take turns: one is loaded while the
+// other is multiplied, its loads back to back at the group's start, one
+// 16-row block after the other, so that a row's bytes reach HBM together
+// (issued piece by piece over both blocks, bf16 is up to 24% slower: 6 rows,
+// 8192 x 28672 82 -> 102 us).  The lanes' share of a group is such that both
+// types sum the same products in the same order, and that a load touches one
+// 128-byte line per row.
+//
+// Groups of four int8 steps (eight loads) leave idle steps at the end of
+// short ranges, and registers for sixteen waves only up to 64 input rows.
+// Calls of sd_linear_q8 in a graph, weights from HBM, four steps (seven waves
+// of 32 columns above 64 rows; under 16 and 65 to 112 rows every load issued
+// as its registers came free) -> two steps: 24 rows, 4096 x 11008 20.6 -> 17.0
+// us; 80 rows, 2048 x 5632 20.7 -> 14.0; 80 rows, 4096 x 11008 33.4 -> 24.2; 6
+// rows, 57344 x 8192 92.0 -> 89.3; 48 rows there 108.3 -> 101.1; 112 rows
+// 140.5 -> 142.5; 128 rows 164.4 -> 157.8.
 //
 // The input rows of a step are copied L2 -> LDS by the buffer_load ... lds
 // DMA into a ring of four slots, three steps ahead.  The copying wave waits
@@ -92,24 +98,24 @@ __device__ __forceinline__ void stream_for(F&& f) {
 // every load in flight (s_waitcnt vmcnt(0) before a chunk's first product),
 // which left HBM idle under the products.
 //
-// Two blocks of 16 weight rows per wave (CB = 2) take half the fragment
+// Two blocks of 16 weight rows per wave (CB = 2, bf16) take half the fragment
 // reads and half the input copies per weight byte.  Measured (kernel trace,
 // medians, weights from HBM; before: one block per wave, a single register
 // group in flight under the products, copies in every wave): 112 rows,
-// 28672 x 4096 bf16 68.0 -> 52.5 us, int8 58.1 -> 43.0 us; 4096 x 14336 bf16
-// 39.0 -> 33.0 us; 36 rows, 57344 x 8192 bf16 185.6 -> 168.7 us (5.6 TB/s),
-// int8 127.9 -> 106.6 us; 6 rows, 28672 x 4096 45.0 -> 40.8 us (5.75 TB/s).
+// 28672 x 4096 68.0 -> 52.5 us; 4096 x 14336 39.0 -> 33.0 us; 36 rows, 57344 x
+// 8192 185.6 -> 168.7 us (5.6 TB/s); 6 rows, 28672 x 4096 45.0 -> 40.8 us
+// (5.75 TB/s).
 template <int RB, int CB, int NW, bool Q8>
 __device__ __forceinline__ void stream_product(const void* w0, size_t block_bytes, const int (&valid)[CB],
                                                bool active, const uint16_t* x, int rows,
                                                int K, int ch0, int ch1, int rot, unsigned char* ring,
                                                floatx4 (&acc)[CB][RB]) {
   constexpr int COPIES = RB * 4;                // 1 KB copies per step
-  constexpr int GS = Q8 ? 4 : 2;                // steps per weight group
-  constexpr int WS = 8 / GS;                    // weight loads per step, lane and 16-row block
+  constexpr int GS = 2;                         // steps per weight group
+  constexpr int WS = Q8 ? 2 : 4;                // weight loads per step, lane and 16-row block
+  constexpr int GL = GS * WS;                   // and per group
   constexpr int SLOT = stream_slot_bytes(RB);
   constexpr uint32_t PAST = 0x80000000u;        // beyond every buffer's range
-  constexpr bool ROLL = Q8 && (RB == 1 || (RB >= 5 && RB <= 7));   // refill piece by piece
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), G = lane >> 4,
             c = lane & 15;
   const int t0 = ch0 * 2, t1 = ch1 * 2;         // steps of the range
@@ -174,19 +180,18 @@ __device__ __forceinline__ void stream_product(const void* w0, size_t block_byte
     wrsrc[cb] = stream_rsrc(static_cast<const unsigned char*>(w0) + cb * block_bytes,
                             (uint32_t)min(max(valid[cb], 0), 16) * row_bytes);
   const uint32_t woff = (uint32_t)c * row_bytes + (uint32_t)G * (Q8 ? 16u : 32u);
-  u32x4 wf[2][CB][8];
-  // piece i of block cb of the group of steps t .. t + GS - 1
-  auto wpiece = [&](u32x4 (&f)[CB][8], int t, int cb, int i) {
-    const int ts = t + i / WS;
-    const uint32_t off = ts < t1 ? (uint32_t)at(ts) * (Q8 ? 128u : 256u) : PAST;
-    const uint32_t in_step = Q8 ? 64u * (i & 1) : 128u * ((i & 3) >> 1) + 16u * (i & 1);
-    f[cb][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wrsrc[cb], (int)(woff + off + in_step), 0, 0));
-  };
-  auto wload = [&](u32x4 (&f)[CB][8], int t) {  // a whole group, block by block
+  u32x4 wf[2][CB][GL];
+  // the group of steps t .. t + GS - 1, block by block
+  auto wload = [&](u32x4 (&f)[CB][GL], int t) {
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) wpiece(f, t, cb, i);
+      for (int i = 0; i < GL; ++i) {
+        const int ts = t + i / WS;
+        const uint32_t off = ts < t1 ? (uint32_t)at(ts) * (Q8 ? 128u : 256u) : PAST;
+        const uint32_t in_step = Q8 ? 64u * (i & 1) : 128u * ((i & 3) >> 1) + 16u * (i & 1);
+        f[cb][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wrsrc[cb], (int)(woff + off + in_step), 0, 0));
+      }
   };
   uint32_t xa[4];                               // fragment addresses of the four products, slot 0
 #pragma unroll
@@ -194,7 +199,7 @@ __device__ __forceinline__ void stream_product(const void* w0, size_t block_byte
 
   // products of one step: s its index within the weight group.  The step's
   // 4 RB fragments are read four at a time, one such unit ahead.
-  auto multiply = [&](u32x4 (&f)[CB][8], int tg, auto stag, auto slot_tag) {
+  auto multiply = [&](u32x4 (&f)[CB][GL], auto stag, auto slot_tag) {
     constexpr int s = decltype(stag)::value, SO = decltype(slot_tag)::value * SLOT;
     u32x4 xf[2][4];
     Pack8 p[CB];
@@ -240,33 +245,18 @@ __device__ __forceinline__ void stream_product(const void* w0, size_t block_byte
           y.u = xf[u & 1][i];
           acc[cb][rb] = mfma_bf16(p[cb].b, y.b, acc[cb][rb]);
         }
-        // a piece's registers are free after its last product
-        if constexpr (ROLL && rb == RB - 1 && j % 2 == 1) {
-#pragma unroll
-          for (int cb = 0; cb < CB; ++cb) wpiece(f, tg + 2 * GS, cb, s * WS + (j >> 1));
-        }
       });
       __builtin_amdgcn_sched_barrier(0);
     });
   };
-  if constexpr (ROLL) {
-    // in the order of the products, which the waits of the loop count on
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb) wpiece(wf[i / 8], t0 + i / 8 * GS, cb, i % 8);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  } else {
-    wload(wf[0], t0);
-  }
+  wload(wf[0], t0);
 #pragma unroll 1
   for (int t = t0; t < t1; t += 2 * GS)
     stream_for<0, 2 * GS>([&](auto st) {
       constexpr int s = decltype(st)::value, gs = s % GS;
       meet();
-      if constexpr (!ROLL && gs == 0) wload(wf[(s / GS + 1) & 1], t + s + GS);
-      multiply(wf[s / GS], t + s - gs, std::integral_constant<int, gs>{}, std::integral_constant<int, s & 3>{});
+      if constexpr (gs == 0) wload(wf[(s / GS + 1) & 1], t + s + GS);
+      multiply(wf[s / GS], std::integral_constant<int, gs>{}, std::integral_constant<int, s & 3>{});
     });
 }
 

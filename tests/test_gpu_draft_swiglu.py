@@ -1,6 +1,5 @@
 """The draft layer with SwiGLU in the gate / up projection, at the edges of
-its tiles: rows around the 16-row blocks, the 64 rows where an int8
-work-group changes its waves, and the 128-row pass; intermediate widths whose
+its tiles: rows around the 16-row blocks and the 128-row pass; intermediate widths whose
 16-pair units fill the last work-group, leave it ragged, or are fewer than
 the compute units; 3 and 5 chunks of the reduction, at each of which some
 work-group starts; one shape whose reduction is split instead.
