@@ -880,6 +880,12 @@ __global__ __launch_bounds__(256) void verify_merge(VerifyArgs a, int keys_per_s
 // (4 channels per lane), in one round of memory accesses; the chunk's weights 2^(lse - max)
 // then rescale a running sum as in the online softmax.  Every shuffle runs
 // on all lanes.  Grid (pairs, ceil(rows per pair / 4)).
+// TWO16: 16-row work-groups in two key groups.  A range that ends in the pair
+// left one partial there, of both groups or of the only tile's, so that only
+// a last range that goes on has two.  Two candidates for every range, half of
+// them empty, double the merge's rounds where a pair spreads over many work-
+// groups (one pair of 30000 keys: 46.7 us so, 33.6 us in one key group).
+template <bool TWO16>
 __global__ __launch_bounds__(256) void verify_stream_merge(VerifyArgs a, int G, int row_groups,
                                                            int KG, int rows_wg, int paged) {
   const int pair = blockIdx.x;
@@ -922,7 +928,8 @@ __global__ __launch_bounds__(256) void verify_stream_merge(VerifyArgs a, int G, 
     auto wstart = [&](int v) { return (int)(qt * (unsigned)v + (rt * (unsigned)v) / (unsigned)G); };
     auto owner = [&](int n) { return (int)((((long long)n + 1) * G - 1) / T); };
     const int wf = owner(U), wl = owner(U + nt - 1);
-    const int ncand = (wl - wf + 1) * KG;
+    const int nw = wl - wf + 1;
+    const int ncand = TWO16 ? nw + (wstart(wl + 1) > U + nt) : nw * KG;
     for (int c0 = 0; c0 < ncand; c0 += 32) {
       const int n = min(32, ncand - c0);
       // lane i < n: slot of candidate c0 + i (key group kg of work-group
@@ -930,12 +937,15 @@ __global__ __launch_bounds__(256) void verify_stream_merge(VerifyArgs a, int G, 
       int sl = -1;
       if (lane < n) {
         const int cand = c0 + lane;
-        const int wv = wf + cand / KG, kg = cand - (cand / KG) * KG;
+        const int wv = TWO16 ? min(wf + cand, wl) : wf + cand / KG;
         const int s0 = wstart(wv), s1 = wstart(wv + 1);
         const int lo = max(U, s0), hi = min(U + nt, s1);
+        const int kg = !TWO16 ? cand - (cand / KG) * KG
+                       : cand == nw ? 1
+                       : s1 <= U + nt && hi - lo == 1 ? (lo - s0) & 1 : 0;
         const int first = s0 + kg + (lo > s0 + kg ? (lo - s0 - kg + KG - 1) / KG * KG : 0);
         if (first < hi) sl = (pair + wv) * KG + kg;
-        if (KG == 2 && kg == 1 && sl >= 0) {
+        if (KG == 2 && !TWO16 && kg == 1 && sl >= 0) {
           // both groups' last tiles in this pair: one combined partial
           const int last0 = s0 + (s1 - 1 - s0) / 2 * 2;
           const int last1 = s0 + 1 + (s1 - 2 - s0) / 2 * 2;
@@ -1116,7 +1126,8 @@ hipError_t launch_verify(const VerifyArgs& a, const VerifyPlan& p, int dtype, hi
     hipLaunchKernelGGL(verify_merge, dim3(a.Hkv * a.B, (p.rows + 3) / 4), dim3(256), 0, st, a,
                        p.keys_per_split, p.nsplit, p.rows_padded, paged ? 1 : 0);
   else if (!p.direct)
-    hipLaunchKernelGGL(verify_stream_merge, dim3(a.B * a.Hkv * p.row_groups, (p.rows_wg + 3) / 4),
+    hipLaunchKernelGGL(p.row_blocks == 1 && p.key_groups == 2 ? verify_stream_merge<true> : verify_stream_merge<false>,
+                       dim3(a.B * a.Hkv * p.row_groups, (p.rows_wg + 3) / 4),
                        dim3(256), 0, st, a, p.stream_wgs, p.row_groups, p.key_groups, p.rows_wg,
                        paged ? 1 : 0);
   return hipGetLastError();

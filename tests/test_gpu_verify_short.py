@@ -41,7 +41,10 @@ def test_verify_short_cache(cap, k, hq, hkv, D, paged, sign):
 
 @pytest.mark.parametrize("kv,k,hq,hkv,D,B,paged", [
     (257, 5, 8, 8, 128, 1, False), (300, 16, 2, 2, 64, 3, True), (1201, 5, 32, 32, 128, 1, False),
-    (2999, 4, 8, 2, 128, 2, True), (1500, 8, 4, 2, 64, 5, False)])
+    (2999, 4, 8, 2, 128, 2, True), (1500, 8, 4, 2, 64, 5, False),
+    # a pair over 47 to 93 work-groups, more than one round of the merge
+    (6001, 4, 4, 1, 128, 1, False), (6000, 16, 2, 2, 64, 2, True), (11999, 5, 3, 3, 128, 1, False),
+    (9000, 8, 2, 1, 64, 5, True)])
 def test_verify_one_row_block_few_tiles(kv, k, hq, hkv, D, B, paged):
     # at most 16 query rows per KV head and few tiles per work-group: two key
     # groups per work-group, ragged lengths with empty and very short ones
