@@ -15,6 +15,9 @@
 //    - `lm_logits_stream` (R <= 128, d % 256 == 0): the weight stream of the
 //      projections, 32 vocabulary rows per wave; one pair per row and
 //      work-group.
+//    - `lm_logits_burst` (R <= 64, short reductions): 16 vocabulary rows per
+//      wave, several work-groups per compute unit; one pair per row and
+//      work-group.
 //    - `lm_logits_bf16` (the other shapes): 16 or 32 vocabulary rows per
 //      wave read 128 bytes per row at a time, the next 64 channels in
 //      flight while the current ones are multiplied; the hidden chunk of 64
@@ -231,11 +234,13 @@ __device__ __forceinline__ Stat write_block(const LmHeadArgs& a, const floatx4& 
 // rows a multiple of a kilobyte apart, few channels of their L2; 16 rows,
 // V = 60000, d = 4096: 114 us in step, 153 us with the starts spread over the
 // XCDs only, 96 us so).
-// Per call, before (16 vocabulary rows per wave, hidden chunks copied by every
-// wave; 128-byte runs for R > 64) and after: d = 4096: 112 rows, V = 32000
-// 105.0 -> 74.4 us; 28 rows, V = 60000 112.8 -> 100.4 us; 12 rows, V = 100001
-// 190.4 -> 156.2 us.  d = 8192, V = 152064: 112 rows 713 -> 551 us, 36 rows
-// 466 -> 461 us, 5 rows 430 -> 445 us (slower).
+// Back-to-back calls, lm_logits_burst or (R > 64) lm_logits_bf16 -> this: d =
+// 4096: 112 rows, V = 32000 95.8 -> 74.8 us; 28 rows, V = 60000 112.8 -> 100.4;
+// 12 rows, V = 100001 188.4 -> 154.4.  d = 8192, V = 152064: 112 rows 713 ->
+// 551, 36 rows 466 -> 461, 5 rows 417.5 -> 424.5.  Up to 24 rows at d = 8192 the
+// two scatter against each other with how the vocabulary divides over their
+// work-groups: over 16 vocabularies of 100000 to 256000 entries this takes
+// 0.83 to 1.04 of the burst kernel's time, 0.967 on average.
 template <int RB>
 __global__ __launch_bounds__(512) void lm_logits_stream(LmHeadArgs a, int base, int extra) {
   constexpr int NW = 8, CB = 2, HROWS = RB * 16;
@@ -273,6 +278,118 @@ __global__ __launch_bounds__(512) void lm_logits_stream(LmHeadArgs a, int base, 
   if (tid < HROWS && tid < a.R) {
     Stat t = wst[0][tid];
     for (int i = 1; i < units; ++i) t = merge(t, wst[i][tid]);
+    reinterpret_cast<float2*>(a.stats)[(size_t)tid * gridDim.x + blockIdx.x] = make_float2(t.m, t.l);
+  }
+}
+
+typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(1))) const void gbl_cvoid;
+
+// Logits for R <= 64 hidden rows and short reductions (use_burst): each wave
+// owns 16 vocabulary rows, and small work-groups, several per compute unit,
+// overlap each other's first loads and last writes, which are most of a short
+// reduction's time.  Per chunk of 256 channels lane (c, G) loads 128
+// contiguous bytes of row c (channels 64 G .. 64 G + 63) as eight back-to-back
+// 16-byte loads, so every row is read in 512-byte runs.  Matrix-core product
+// i takes the i-th load of every lane, i.e. channels 64 G + 8 i .. + 7: a
+// fixed permutation of the chunk's channels, which the hidden fragments
+// follow.  The hidden chunk of all rows (RB x 16 rows x 512 bytes) goes
+// HBM/L2 -> LDS by the global_load_lds DMA into two buffers; pieces of row r
+// sit at slot piece ^ (r & 15) so the 16 rows read at one piece hit 16
+// distinct bank groups.
+//
+// With nfull >= 0 the first nfull work-groups give every wave its
+// block and the later ones leave their last wave without one (it only
+// moves its share of the hidden chunks): the grid then holds a whole number
+// of work-groups per compute unit with the larger ones dispatched first, so
+// no unit streams more than one 16-row block above the mean.
+template <int RB, int NW>
+__global__ __launch_bounds__(NW * 64) void lm_logits_burst(LmHeadArgs a, int nfull) {
+  constexpr int HROWS = RB * 16;
+  constexpr int HPIECES = HROWS * 32;          // 16-byte pieces of one hidden chunk
+  constexpr int DMA = HPIECES / (NW * 64);     // copies per thread and chunk
+  static_assert(HPIECES % (NW * 64) == 0, "whole copies per thread");
+  __shared__ __align__(16) unsigned char hbuf[2][HPIECES * 16];
+  __shared__ Stat wst[NW][HROWS];              // per wave: its blocks' statistics of every hidden row
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), G = lane >> 4, c = lane & 15;
+  const int wg = blockIdx.x;
+  const bool full = nfull < 0 || wg < nfull;
+  const int unit0 = full ? wg * NW : nfull * NW + (wg - nfull) * (NW - 1);
+  const int v0 = (unit0 + w) * 16;
+  const int d = a.d, V = a.V, R = a.R;
+  const uint16_t* W = static_cast<const uint16_t*>(a.weight);
+  const uint16_t* H = static_cast<const uint16_t*>(a.hidden);
+  // row c of this wave (clamped; results of rows >= V are discarded)
+  const u32x4* wsrc = reinterpret_cast<const u32x4*>(W + (size_t)min(v0 + c, V - 1) * d + 64 * G);
+  // copy j of this thread moves piece P = (w * DMA + j) * 64 + lane of the
+  // chunk: hidden row P / 32 (clamped; padded rows are discarded), LDS slot
+  // P % 32 holding global piece slot ^ (row & 15)
+  const uint16_t* hsrc[DMA];
+#pragma unroll
+  for (int j = 0; j < DMA; ++j) {
+    const int P = (w * DMA + j) * 64 + lane;
+    const int row = P >> 5, slot = P & 31;
+    hsrc[j] = H + (size_t)min(row, R - 1) * d + ((slot ^ (row & 15)) * 8);
+  }
+  auto issue_hidden = [&](int n, int buf) {
+#pragma unroll
+    for (int j = 0; j < DMA; ++j)
+      __builtin_amdgcn_global_load_lds((gbl_cvoid*)(hsrc[j] + n * 256),
+                                       (lds_void*)(&hbuf[buf][(w * DMA + j) * 1024]), 16, 0, 0);
+  };
+
+  floatx4 acc[RB];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) acc[rb] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const int nch = d / 256;
+  issue_hidden(0, 0);
+  const bool idle = !full && w == NW - 1;
+  if (idle) {
+    // same copies, waits and barriers as the other waves, no weight rows
+#pragma unroll 1
+    for (int n = 0; n < nch; ++n) {
+      wait_vm_then_barrier<0>();
+      if (n + 1 < nch) issue_hidden(n + 1, (n & 1) ^ 1);
+    }
+  } else {
+#pragma unroll 1
+    for (int n = 0; n < nch; ++n) {
+      const int buf = n & 1;
+      u32x4 wf[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) wf[i] = wsrc[n * 32 + i];
+      // the weight loads are the newest: everything older (this thread's
+      // copies of chunk n) has landed; after the barrier every wave's copies
+      // have, and every wave is done reading the other buffer
+      wait_vm_then_barrier<8>();
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+          const int row = rb * 16 + c;
+          Pack8 x, y;
+          x.u = wf[i];
+          y.u = *reinterpret_cast<const u32x4*>(&hbuf[buf][(row * 32 + ((8 * G + i) ^ c)) * 16]);
+          acc[rb] = mfma_bf16(x.b, y.b, acc[rb]);
+        }
+      }
+      if (n + 1 < nch) issue_hidden(n + 1, buf ^ 1);
+    }
+  }
+  // scaled logits to probs; the statistics of this work-group's blocks,
+  // merged over its waves, as one (max, sum) pair per hidden row at
+  // stats[r * gridDim.x + blockIdx.x]
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const Stat st = idle ? Stat{-INFINITY, 0.f} : write_block(a, acc[rb], v0, rb * 16 + c);
+    if (G == 0) wst[w][rb * 16 + c] = st;
+  }
+  __syncthreads();
+  if (tid < HROWS && tid < R) {
+    Stat t = wst[0][tid];
+#pragma unroll
+    for (int i = 1; i < NW; ++i) t = merge(t, wst[i][tid]);
     reinterpret_cast<float2*>(a.stats)[(size_t)tid * gridDim.x + blockIdx.x] = make_float2(t.m, t.l);
   }
 }
@@ -364,13 +481,52 @@ __global__ __launch_bounds__(256) void lm_normalize(LmHeadArgs a, int npairs) {
   }
 }
 
+// Up to 64 rows: the burst kernel where the reduction is short and the
+// vocabulary long enough to give every compute unit several of its work-groups
+// (calls in a graph, stream -> burst: 8 rows, d = 256, V = 32000 12.1 -> 10.9
+// us, V = 128256 28.1 -> 22.2; 40 rows, d = 512, V = 128256 48.8 -> 44.2; 8
+// rows, d = 1024, V = 32000 22.2 -> 20.0), and at every vocabulary for a single
+// chunk (64 rows, V = 1000 9.5 -> 7.9).  The stream takes shorter vocabularies
+// (8 rows, d = 512, V = 4000 8.2 us, burst 8.6), rows of probabilities that
+// start unaligned (28 rows, d = 768, V = 50257 30.4 and 32.4) and longer
+// reductions (8 rows, d = 1536, V = 32000 26.3 and 27.0).
+bool use_burst(int d, int V, int cus) {
+  if (d % 256 != 0 || d > 1024) return false;
+  return d == 256 || (V % 4 == 0 && V > 3 * 32 * (cus > 0 ? cus : 256));
+}
+
 // Launches the logits kernel; *npairs receives the statistics pairs it
-// writes per row (one per work-group for the long-row kernel, one per
-// 16-entry block otherwise).
+// writes per row (one per work-group for the stream and burst kernels, one
+// per 16-entry block otherwise).
 template <int RB>
 hipError_t launch_rb(const LmHeadArgs& a, hipStream_t st, int* npairs) {
+  if constexpr (RB <= 4) {
+    if (use_burst(a.d, a.V, a.cus)) {
+      if (a.V >= 65536) {
+        // G work-groups, a multiple of the unit count, of 8 or 7 blocks
+        // (nb - 7 G of 8) when such a G covers the nb blocks
+        const int nb = (a.V + 15) / 16, g8 = (nb + 7) / 8;
+        int grid = g8, nfull = -1;
+        if (a.cus > 0) {
+          const int G = (g8 + a.cus - 1) / a.cus * a.cus;
+          if (G > g8 && 7LL * G <= nb) {
+            grid = G;
+            nfull = nb - 7 * G;
+          }
+        }
+        hipLaunchKernelGGL((lm_logits_burst<RB, 8>), dim3(grid), dim3(512), 0, st, a, nfull);
+        *npairs = grid;
+      } else {
+        hipLaunchKernelGGL((lm_logits_burst<RB, 4>), dim3((a.V + 63) / 64), dim3(256), 0, st, a, -1);
+        *npairs = (a.V + 63) / 64;
+      }
+      return hipGetLastError();
+    }
+  }
   if constexpr (RB <= 8) {
-    if (a.d % kStreamChunk == 0 && RB <= stream_row_blocks(a.d)) {
+    // one chunk under more than 64 rows: the general kernel (112 rows, V =
+    // 1000 13.0 us on the stream, 9.6 us; V = 128256 69.5 and 63.3)
+    if (a.d % kStreamChunk == 0 && (RB <= 4 || a.d > kStreamChunk) && RB <= stream_row_blocks(a.d)) {
       // rounds of up to seven units per work-group, one work-group per
       // compute unit (its registers hold no second one; two smaller ones, of
       // one 16-row block per wave, measured the same to 6% slower)

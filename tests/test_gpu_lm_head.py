@@ -62,17 +62,26 @@ def test_lm_head_long_video_every_row():
                                        (17, 192, 300, 20.0), (65, 64, 129, 1.0),
                                        (130, 128, 2050, 0.7),
                                        # widths d % 256 == 0 with R <= 128 (the
-                                       # weight stream): one entry, partial
-                                       # units, odd chunk counts, one to eight
-                                       # 16-row blocks, one and two rounds of
-                                       # work-groups with starts at every
-                                       # chunk, ragged ends and unaligned rows
+                                       # weight stream, or the burst kernel for
+                                       # R <= 64 and short reductions): one
+                                       # entry, partial units, odd chunk
+                                       # counts, one to eight 16-row blocks,
+                                       # one and two rounds of work-groups with
+                                       # starts at every chunk, ragged ends and
+                                       # unaligned rows
                                        (1, 256, 1, 1.0), (3, 256, 50, 0.5),
                                        (16, 512, 1000, 1.0), (33, 768, 129, 2.0),
                                        (64, 256, 65600, 0.7), (49, 1024, 70001, 0.3),
                                        (65, 768, 9001, 1.0), (80, 1280, 70001, 0.7),
                                        (90, 1280, 9001, 0.5), (112, 512, 20017, 1.0),
-                                       (128, 768, 20017, 0.7)])
+                                       (128, 768, 20017, 0.7),
+                                       # burst and stream on either side of the
+                                       # rule's bounds; work-groups of seven
+                                       # and eight waves with blocks
+                                       (33, 768, 24576, 1.0), (33, 768, 24580, 1.0),
+                                       (17, 1024, 30004, 0.7), (64, 1280, 30004, 0.7),
+                                       (20, 512, 90004, 1.0), (64, 256, 30001, 1.0),
+                                       (65, 256, 9001, 1.0)])
 def test_lm_head_edge_shapes(R, d, V, tau):
     # ragged rows (row blocks of 16), ragged vocabulary (units of 32 or tiles
     # of 64 / 128, blocks of 16), odd channel groups, extreme temperatures
