@@ -345,9 +345,12 @@ __global__ __launch_bounds__(kEpiThreads) void epi_swiglu(const float* part, int
 // reduction in one split: act[r][i] = silu(g) * u, bf16, g and u the products
 // with weight rows i and I + i times the row's norm factor.  A unit is 16
 // gate rows and their 16 up rows: the two blocks of a wave, or two waves
-// that meet through LDS (the waves of int8 rows, see LinearCfg).  Same bits
-// as linear_partial and epi_swiglu, without the partials' way through memory
-// and the second launch.
+// that meet through LDS (the waves of int8 rows, see LinearCfg).  The same
+// products as linear_partial's, without the partials' way through memory and
+// the second launch, but summed from another chunk on (the start follows the
+// work-group's index, and a column lies in another one) and never in splits,
+// so the float32 sums may round differently.  Bf16 and int8 weights of the
+// same values share the order and give the same bits.
 struct SwigluArgs {
   __bf16* act;
   const float* ss;

@@ -157,7 +157,7 @@ struct LinearArgs {
 struct LinearPlan {
   int row_blocks;  // 16-row blocks per pass (1..8)
   int passes;      // passes over the weight (ceil(R / 128) up to 2^22 channels)
-  int cols;        // output columns per work-group: 16 per wave that owns columns
+  int cols;        // output columns per work-group: 64 .. 224, whole 32-column units
   int ksplit;      // splits of the reduction
   long long load;  // relative time of the most loaded compute unit
   size_t part_bytes;
