@@ -11,7 +11,8 @@
 // projection streams its weight once and is bound by HBM.  All five are
 // built around the weight stream of skinny_stream.hpp: a work-group of eight
 // waves, of which up to seven own 32 output columns each over a range of
-// 256-channel chunks of the reduction and one copies the input rows.  A
+// 256-channel chunks of the reduction and one copies the input rows (int8
+// weights: sixteen waves, up to fourteen of 16 columns).  A
 // compute unit streams weights at a bounded rate, so the planner sizes the
 // column groups and reduction splits to give every unit the same load; each
 // split writes fp32 partial sums, and one epilogue launch per projection
@@ -585,7 +586,8 @@ SemiArPlan plan_semi_ar(int B, int r, int d, int Hq, int Hkv, int I, int Lmax, i
   // plan above (plan_linear's load; units of 16 gate and 16 up rows).  Fused
   // against unfused: one sequence of 6 rows with its head (d = 4096, I =
   // 11008) 166.4 against 170.2 us, a layer of 4 sequences at d = 8192, I =
-  // 28672 391 against 403 us (bf16) and 266.1 against 267.9 (int8).  Where
+  // 28672 391 against 396 us (bf16) and within 0.4% of each other (int8; 8
+  // sequences of 9 rows 292 against 299).  Where
   // the load would grow by a third (16 sequences, d = 4096, I = 14336) it
   // gains nothing: 182.8 against 182.9 us.
   const long long ncu = std::max(cus, 1);
